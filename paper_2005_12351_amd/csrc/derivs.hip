@@ -13,27 +13,28 @@
 //             derivatives of 1/r (Eq. 6 applied to a point source's own
 //             expansion).
 // FP64 throughout, from the tree's FP64 expansions and sorted FP64 moments,
-// in both precisions of the tree.  FMM: one workgroup per leaf, the leaf's
-// local row staged in LDS, every thread one target walking the leaf's P2P
-// list.  Barnes-Hut: one wavefront per particle; the wave walks the
+// in both precisions of the tree.  FMM: one workgroup per leaf, its threads a
+// (target, slice) grid as in the near-field kernels: the sources of the leaf's
+// P2P list staged in LDS with their source tensors formed, each slice taking
+// every ns-th of them, the pair's derivative tensor written out at compile
+// time; the leaf's local row in LDS, the slices sharing out its terms.
+// Barnes-Hut: one wavefront per particle; the wave walks the
 // particle's traversal, builds an accepted cell's derivative tensor in LDS
 // (one component per lane) and contracts it with the cell's multipole row
 // (one term per lane), and splits an unaccepted leaf's sources over lanes.
+#include <utility>
+
 #include "fmm_internal.h"
+#include "p2p_kernel.h"
 
 namespace {
 
-constexpr int kDT = 64;   // threads per leaf
-
 struct DerivArgs {
-    const int32_t *leaves, *ptr, *src, *perm;
-    const DevCell *cells;
-    const double *xs;      // sorted positions, SoA
-    const double *mom;     // sorted moments, w per particle
+    P2PArgs near;          // leaves, P2P lists, dispatch order, cells, positions, moments, root geometry
+    const int32_t *perm;
     const double *L;       // normalised locals, nl per cell (harmonic basis: nlh, the n_z <= 1 part)
     double *out;           // nk per particle, caller order
-    int n, nl, nlh, q, w, smask;
-    double h, lo[3];
+    int nl, nlh, q, w, smask;
 };
 
 // D_k(r) = d^k (1/|r|) by the Hermite form of the derivatives of f(r^2/2),
@@ -153,81 +154,277 @@ __device__ __forceinline__ void pair_derivs_add(double rx, double ry, double rz,
     }
 }
 
-template <int K>
-__global__ __launch_bounds__(kDT) void derivs_kernel(DerivArgs a)
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>)
+template <typename F, int... I>
+__device__ __forceinline__ void unrolled(F &&f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void unrolled(F &&f)
+{
+    unrolled(f, std::make_integer_sequence<int, N>{});
+}
+
+// multi-index number c of order k, at compile time
+struct MI3 {
+    int x, y, z;
+};
+constexpr MI3 mi_const(int k, int c)
+{
+    int x = k, left = c;
+    while (left > k - x) {
+        left -= k - x + 1;
+        --x;
+    }
+    const int y = k - x - left;
+    return MI3{x, y, k - x - y};
+}
+// c(n, a) = n! / (2^a a! (n - 2a)!) of the Hermite form
+constexpr double hermite_const(int n, int a)
+{
+    double v = 1.0;
+    for (int i = n; i > n - 2 * a; --i) v *= i;
+    for (int i = 1; i <= a; ++i) v /= 2.0 * i;
+    return v;
+}
+
+// acc[c] += sum_{|m|=S} T_m D_{m+k_c}(r), |k_c| = K: the K-th derivatives of
+// the potential of one source of order S with source tensor T(m).  Only the
+// derivative components of order S + K are formed, each as its Hermite sum
+// with every index and coefficient a constant.
+template <int K, int S, typename TF>
+__device__ __forceinline__ void pair_derivs_const(double rx, double ry, double rz, double ir, TF &&T,
+                                                  double (&acc)[(K + 1) * (K + 2) / 2])
+{
+    constexpr int Q = K + S, NQ = (Q + 1) * (Q + 2) / 2, NM = (S + 1) * (S + 2) / 2, NK = (K + 1) * (K + 2) / 2;
+    const double ir2 = ir * ir;
+    double px[Q + 1], py[Q + 1], pz[Q + 1], F[Q + 1], D[NQ];
+    px[0] = py[0] = pz[0] = 1.0;
+    F[0] = ir;
+    unrolled<Q>([&](auto d_) {
+        constexpr int d = decltype(d_)::value + 1;
+        px[d] = d == 1 ? rx : px[d - 1] * rx;
+        py[d] = d == 1 ? ry : py[d - 1] * ry;
+        pz[d] = d == 1 ? rz : pz[d - 1] * rz;
+        F[d] = F[d - 1] * (ir2 * -(2.0 * d - 1.0));
+    });
+    unrolled<NQ>([&](auto i_) {
+        constexpr MI3 k = mi_const(Q, decltype(i_)::value);
+        double v = 0.0;
+        unrolled<(k.x / 2 + 1) * (k.y / 2 + 1) * (k.z / 2 + 1)>([&](auto t_) {
+            constexpr int t = decltype(t_)::value;
+            constexpr int az = t % (k.z / 2 + 1), ay = t / (k.z / 2 + 1) % (k.y / 2 + 1),
+                          ax = t / (k.z / 2 + 1) / (k.y / 2 + 1);
+            constexpr double c = hermite_const(k.x, ax) * hermite_const(k.y, ay) * hermite_const(k.z, az);
+            v = fma(c * F[Q - ax - ay - az], px[k.x - 2 * ax] * py[k.y - 2 * ay] * pz[k.z - 2 * az], v);
+        });
+        D[decltype(i_)::value] = v;
+    });
+    unrolled<NM>([&](auto m_) {
+        constexpr MI3 m = mi_const(S, decltype(m_)::value);
+        const double t = T(decltype(m_)::value);
+        unrolled<NK>([&](auto c_) {
+            constexpr MI3 k = mi_const(K, decltype(c_)::value);
+            acc[decltype(c_)::value] =
+                fma(t, D[mindex(m.x + k.x, m.y + k.y, m.z + k.z) - nterms(Q - 1)], acc[decltype(c_)::value]);
+        });
+    });
+}
+
+// The derivatives of order K at every particle of a leaf.  What bounds it is
+// FP64 issue: per pair about 100 operations for dipoles at K = 2.  The grid of
+// 256 threads is (target, slice) with floor(256 / targets) slices, as in the
+// near-field kernels, so leaves of 10 to 60 particles fill the workgroup.
+// ONE >= 0: the only source order present; -1: any mask, told at run time.
+// (An earlier form, one wave a leaf with run-time multi-indices, spent its
+// time in index arithmetic and scratch memory: 9.44 ms for 20 011 dipoles at
+// K = 2, ncrit 64, against 0.106 ms for this one.)
+constexpr int kDT = kPT;      // threads per leaf
+constexpr int kDChunk = 128;  // staged sources
+template <int K, int ONE>
+__global__ __launch_bounds__(kDT) void derivs_kernel(DerivArgs d)
 {
     constexpr int NK = (K + 1) * (K + 2) / 2;
-    __shared__ double sL[nterms(FMM_P_MAX)];
-    const int lk = blockIdx.x;
+    constexpr int W = ONE < 0 ? 20 : (ONE + 1) * (ONE + 2) / 2;   // source tensor components staged
+    constexpr int EMAX = FMM_P_MAX + 1;
+    constexpr int kCube = EMAX * EMAX * EMAX;
+    // one area for the leaf's local (a cube of edge q + 1 indexed by
+    // multi-index), then the staged sources, then the slices' sums
+    constexpr int kStage = (3 + W) * kDChunk, kRed = NK * kDT;
+    constexpr int kArea = kCube > kStage ? (kCube > kRed ? kCube : kRed) : (kStage > kRed ? kStage : kRed);
+    __shared__ double area[kArea];
+    __shared__ int wstart[kPList], wfirst[kPList];
+    __shared__ float4 wgeo[kPList];
+    __shared__ int sh[kPT / 64];
+    __shared__ int wself;
+    const P2PArgs &a = d.near;
+    const int tid = threadIdx.x;
+    const int lk = a.order[blockIdx.x];
     const int b = a.leaves[lk];
     const DevCell cb = a.cells[b];
-    if (a.nlh > 0) {
-        // harmonic basis: the row is rebuilt from its n_z <= 1 components,
-        // (a, b, 2j + r) = (-1)^j sum_i C(j, i) (a + 2i, b + 2(j - i), r)
-        const double *R = a.L + (size_t)b * a.nlh;
-        for (int i = threadIdx.x; i < a.nl; i += kDT) {
-            int nx, ny, nz;
-            mi_at(i, nx, ny, nz);
-            const int j = nz >> 1, r = nz & 1;
-            double acc = 0.0, w = 1.0;
-            for (int k = 0; k <= j; ++k) {
-                acc = fma(w, R[hindex(nx + 2 * k, ny + 2 * (j - k), r)], acc);
-                w = w * (j - k) / (k + 1);
-            }
-            sL[i] = (j & 1) ? -acc : acc;
-        }
-    } else {
-        for (int i = threadIdx.x; i < a.nl; i += kDT) sL[i] = a.L[(size_t)b * a.nl + i];
-    }
-    __syncthreads();
+    const int e0 = a.ptr[lk], e1 = a.ptr[lk + 1];
     const double r = ldexp(1.0, kMaxLevel - cb.level) * a.h;
     const double zb[3] = {a.lo[0] + (double)(2 * cb.ix + 1) * r, a.lo[1] + (double)(2 * cb.iy + 1) * r,
                           a.lo[2] + (double)(2 * cb.iz + 1) * r};
     const size_t n = a.n;
-    int kidx[NK][3];
-#pragma unroll
-    for (int c = 0; c < NK; ++c) mi_of(K, c, kidx[c][0], kidx[c][1], kidx[c][2]);
-    for (int t = threadIdx.x; t < cb.count; t += kDT) {
-        const int i = cb.first + t;
+    const int E = d.q + 1;
+    for (int tg0 = 0; tg0 < cb.count; tg0 += kDT) {
+        const int cs = min(kDT, cb.count - tg0);
+        const int ns = kDT / cs;
+        const int t = tid % cs, sl = tid / cs;
+        const bool act = sl < ns;
+        const int i = cb.first + tg0 + t;
         const double x = a.xs[i], y = a.xs[n + i], z = a.xs[2 * n + i];
         double acc[NK];
 #pragma unroll
         for (int c = 0; c < NK; ++c) acc[c] = 0.0;
-        // far field: Eq. 10 on the normalised local
-        if (K <= a.q) {
+        __syncthreads();
+        // far field: Eq. 10 on the normalised local, the slices taking every
+        // ns-th n_x
+        for (int it = tid; it < d.nl; it += kDT) {
+            int nx, ny, nz;
+            mi_at(it, nx, ny, nz);
+            double v;
+            if (d.nlh > 0) {
+                // harmonic basis: the row is rebuilt from its n_z <= 1 components,
+                // (a, b, 2j + r) = (-1)^j sum_i C(j, i) (a + 2i, b + 2(j - i), r)
+                const double *R = d.L + (size_t)b * d.nlh;
+                const int j = nz >> 1, rr = nz & 1;
+                double w = 1.0;
+                v = 0.0;
+                for (int k = 0; k <= j; ++k) {
+                    v = fma(w, R[hindex(nx + 2 * k, ny + 2 * (j - k), rr)], v);
+                    w = w * (j - k) / (k + 1);
+                }
+                if (j & 1) v = -v;
+            } else {
+                v = d.L[(size_t)b * d.nl + it];
+            }
+            area[(nx * E + ny) * E + nz] = v;
+        }
+        __syncthreads();
+        if (act) {
             const double e[3] = {(x - zb[0]) / r, (y - zb[1]) / r, (z - zb[2]) / r};
-            const int qk = a.q - K;
+            const int qk = d.q - K;
+            int off[NK];
+            unrolled<NK>([&](auto c_) {
+                constexpr MI3 k = mi_const(K, decltype(c_)::value);
+                off[decltype(c_)::value] = (k.x * E + k.y) * E + k.z;
+            });
             double ax = 1.0;
-            for (int nx = 0; nx <= qk; ++nx) {
+            int done = 0;   // ax = e_x^done / done!
+            for (int nx = sl; nx <= qk; nx += ns) {
+                for (; done < nx; ++done) ax *= e[0] / (done + 1);
                 double ay = ax;
                 for (int ny = 0; nx + ny <= qk; ++ny) {
                     double az = ay;
                     for (int nz = 0; nx + ny + nz <= qk; ++nz) {
+                        const double *c0 = area + (nx * E + ny) * E + nz;
 #pragma unroll
-                        for (int c = 0; c < NK; ++c)
-                            acc[c] = fma(az, sL[mindex(nx + kidx[c][0], ny + kidx[c][1], nz + kidx[c][2])], acc[c]);
+                        for (int c = 0; c < NK; ++c) acc[c] = fma(az, c0[off[c]], acc[c]);
                         az *= e[2] / (nz + 1);
                     }
                     ay *= e[1] / (ny + 1);
                 }
-                ax *= e[0] / (nx + 1);
             }
-            const double sc = pow(r, -(double)(K + 1));
+            double sc = 1.0 / r;
+            const double ir = sc;
+#pragma unroll
+            for (int k = 0; k < K; ++k) sc *= ir;
 #pragma unroll
             for (int c = 0; c < NK; ++c) acc[c] *= sc;
         }
         // near field: every source of the leaf's P2P list but the target
-        for (int e = a.ptr[lk]; e < a.ptr[lk + 1]; ++e) {
-            const DevCell cs = a.cells[a.src[e]];
-            for (int j = cs.first; j < cs.first + cs.count; ++j) {
-                if (j == i) continue;
-                const double rx = x - a.xs[j], ry = y - a.xs[n + j], rz = z - a.xs[2 * n + j];
-                pair_derivs_add<K>(rx, ry, rz, a.mom + (size_t)a.w * j, a.smask, kidx, acc);
+        for (int w0 = e0; w0 < e1; w0 += kPList) {
+            const int nw = min(kPList, e1 - w0);
+            __syncthreads();
+            if (tid == 0) wself = -1;
+            __syncthreads();
+            const int nsw = p2p_window(a, cb, b, w0, nw, wstart, wfirst, wgeo, &wself, sh);
+            for (int c0 = 0; c0 < nsw; c0 += kDChunk) {
+                const int nc = min(kDChunk, nsw - c0);
+                __syncthreads();
+                // record j: x, y, z and the source tensors of the orders present
+                for (int j = tid; j < nc; j += kDT) {
+                    const int q = p2p_entry(wstart, nw, c0 + j);
+                    const size_t pj = (size_t)wfirst[q] + (c0 + j - wstart[q]);
+                    double *o = area + (3 + W) * j;
+                    o[0] = a.xs[pj];
+                    o[1] = a.xs[n + pj];
+                    o[2] = a.xs[2 * n + pj];
+                    int at = 0;
+                    for (int s = 0; s < 4; ++s) {
+                        if (ONE >= 0 ? s != ONE : !(d.smask & (1 << s))) continue;
+                        double S[10];
+                        source_of(s, a.m64 + pj * d.w + at, S);
+                        const int nm = (s + 1) * (s + 2) / 2;
+#pragma unroll
+                        for (int c = 0; c < 10; ++c)
+                            if (c < nm) o[3 + at + c] = S[c];
+                        at += nm;
+                    }
+                }
+                __syncthreads();
+                if (act) {
+                    const int jself = wself >= 0 ? wself + tg0 + t - c0 : -1;
+                    for (int j = sl; j < nc; j += ns) {
+                        if (j == jself) continue;
+                        const double *o = area + (3 + W) * j;
+                        const double rx = x - o[0], ry = y - o[1], rz = z - o[2];
+                        const double ir = rsq_f64(rx * rx + ry * ry + rz * rz);
+                        const double *m = o + 3;
+                        auto T = [&](int c) { return m[c]; };
+                        if constexpr (ONE >= 0) {
+                            pair_derivs_const<K, ONE>(rx, ry, rz, ir, T, acc);
+                        } else {
+                            if (d.smask & 1) {
+                                pair_derivs_const<K, 0>(rx, ry, rz, ir, T, acc);
+                                m += 1;
+                            }
+                            if (d.smask & 2) {
+                                pair_derivs_const<K, 1>(rx, ry, rz, ir, T, acc);
+                                m += 3;
+                            }
+                            if (d.smask & 4) {
+                                pair_derivs_const<K, 2>(rx, ry, rz, ir, T, acc);
+                                m += 6;
+                            }
+                            if (d.smask & 8) pair_derivs_const<K, 3>(rx, ry, rz, ir, T, acc);
+                        }
+                    }
+                }
             }
         }
-        double *o = a.out + (size_t)NK * a.perm[i];
+        // the slices' sums, in slice order
+        __syncthreads();
 #pragma unroll
-        for (int c = 0; c < NK; ++c) o[c] = acc[c];
+        for (int c = 0; c < NK; ++c) area[c * kDT + tid] = act ? acc[c] : 0.0;
+        __syncthreads();
+        if (tid < cs) {
+            double v[NK];
+#pragma unroll
+            for (int c = 0; c < NK; ++c) v[c] = 0.0;
+            for (int k = 0; k < ns; ++k)
+#pragma unroll
+                for (int c = 0; c < NK; ++c) v[c] += area[c * kDT + tid + k * cs];
+            double *o = d.out + (size_t)NK * d.perm[i];
+#pragma unroll
+            for (int c = 0; c < NK; ++c) o[c] = v[c];
+        }
+    }
+}
+
+template <int K>
+void derivs_launch(const DerivArgs &a, unsigned nleaves, hipStream_t s)
+{
+    const dim3 g(nleaves), bl(kDT);
+    switch (a.smask) {
+    case 1: hipLaunchKernelGGL((derivs_kernel<K, 0>), g, bl, 0, s, a); break;
+    case 2: hipLaunchKernelGGL((derivs_kernel<K, 1>), g, bl, 0, s, a); break;
+    case 4: hipLaunchKernelGGL((derivs_kernel<K, 2>), g, bl, 0, s, a); break;
+    case 8: hipLaunchKernelGGL((derivs_kernel<K, 3>), g, bl, 0, s, a); break;
+    default: hipLaunchKernelGGL((derivs_kernel<K, -1>), g, bl, 0, s, a); break;
     }
 }
 
@@ -381,28 +578,29 @@ hipError_t launch_derivs(fmm_tree *t, int K, double *out, hipStream_t s)
 {
     if (t->nleaves == 0) return hipSuccess;
     DerivArgs a;
-    a.leaves = t->d_leaves;
-    a.ptr = t->d_p2p_ptr;
-    a.src = t->d_p2p_src;
+    a.near = P2PArgs{};
+    a.near.leaves = t->d_leaves;
+    a.near.ptr = t->d_p2p_ptr;
+    a.near.src = t->d_p2p_src;
+    a.near.order = t->d_p2p_order;
+    a.near.cells = t->d_cells;
+    a.near.xs = t->d_x;
+    a.near.m64 = t->d_mom;
+    a.near.n = (int)t->ht.n;
+    a.near.h = t->ht.h;
+    for (int d = 0; d < 3; ++d) a.near.lo[d] = t->ht.lo[d];
     a.perm = t->d_perm;
-    a.cells = t->d_cells;
-    a.xs = t->d_x;
-    a.mom = t->d_mom;
     a.L = t->d_L64;
     a.out = out;
-    a.n = (int)t->ht.n;
     a.q = t->p - t->order;
     a.nl = nterms(a.q);
     a.nlh = t->basis == FMM_M2L_HARMONIC ? hterms(a.q) : 0;
     a.w = mask_width(t->smask);
     a.smask = t->smask;
-    a.h = t->ht.h;
-    for (int d = 0; d < 3; ++d) a.lo[d] = t->ht.lo[d];
-    const dim3 g((unsigned)t->nleaves), bl(kDT);
     switch (K) {
-    case 1: hipLaunchKernelGGL(derivs_kernel<1>, g, bl, 0, s, a); break;
-    case 2: hipLaunchKernelGGL(derivs_kernel<2>, g, bl, 0, s, a); break;
-    case 3: hipLaunchKernelGGL(derivs_kernel<3>, g, bl, 0, s, a); break;
+    case 1: derivs_launch<1>(a, (unsigned)t->nleaves, s); break;
+    case 2: derivs_launch<2>(a, (unsigned)t->nleaves, s); break;
+    case 3: derivs_launch<3>(a, (unsigned)t->nleaves, s); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
