@@ -61,7 +61,10 @@ TILE = 64
 # workgroup); the defaults are the measured best on gfx950
 DEFAULTS = {"acc32": 128, "m32": 64, "acc64": 64, "m64": 32, "dgroup32": 32, "dgroup64": 16, "pipeline": 1,
             "mpre": 0, "launder": 1, "scale_branch": 0, "minwaves": 0, "wgw": 4, "fairprio": 1,
-            "mch": 32, "mdist": 4, "mwaves": 2, "mbarrier": 1, "mbalance": 0, "mpipe": 1, "malign": 1}
+            "mdist": 4}
+
+ROW_LINE = 32           # FP32 coefficients of a 128-byte line: the chunk of the matrix-core kernels
+NQ = ROW_LINE // 4      # its float4s
 
 
 def orders(p):
@@ -349,35 +352,19 @@ static int occ_{name}()
     return "\n".join(L) + "\n" + launcher, meta
 
 
-def mfma_schedule(p, s, mch, dist, balance=False):
+def mfma_schedule(p, s, mch, dist):
     """Multiply-add slots (j, g) of the harmonic contraction for the matrix
     cores, in issue order, with accumulator copies: a slot whose output group
     was used fewer than `dist` slots before goes to another copy of that
     group's accumulators (added together at the end), so that no MFMA waits
     for the previous one's result.  Returns the chunks of the multipole row
     (lists of j, at most `mch`, starting at multiples of 4) and per chunk the
-    slots as (j, g, copy).  balance: the chunks take whole quads of j (one
-    vector load each) so that they hold about the same number of slots,
-    low orders (many slots) beside high orders (few)."""
+    slots as (j, g, copy)."""
     ns = reduced(orders(p - s))
     ms = reduced(orders(p)[nterms(s - 1):])
     nl = len(ns)
     ng = (nl + 3) // 4
     chunks = [list(range(c, min(len(ms), c + mch))) for c in range(0, len(ms), mch)]
-    if balance:
-        def nslots(j):
-            return sum(1 for g in range(ng)
-                       if any(sum(ns[i]) + sum(ms[j]) <= p for i in range(4 * g, min(nl, 4 * g + 4))))
-        quads = [list(range(q, min(len(ms), q + 4))) for q in range(0, len(ms), 4)]
-        k = len(chunks)
-        cost = sorted(((sum(nslots(j) for j in qd), qi) for qi, qd in enumerate(quads)), reverse=True)
-        bins = [[] for _ in range(k)]
-        load = [0] * k
-        for c, qi in cost:
-            b = min((b for b in range(k) if len(bins[b]) < mch // 4), key=lambda b: load[b])
-            bins[b].append(qi)
-            load[b] += c
-        chunks = [[j for qi in sorted(bn) for j in quads[qi]] for bn in bins if bn]
     out = []
     for ch in chunks:
         queues = {}
@@ -414,6 +401,16 @@ def mfma_schedule(p, s, mch, dist, balance=False):
     return chunks, out
 
 
+def mfma_waves(p, s):
+    """Waves per SIMD (= workgroups per CU) of the matrix-core kernels, held
+    by the launch bound: what the registers allow with the accumulators (one
+    per local output, and copies) beside a chunk of rows and its operands.
+    The host cuts the work into that many pieces per CU, so this number also
+    fixes the order of the FP32 sums."""
+    nl = pad(len(reduced(orders(p - s))), 4)
+    return 4 if nl <= 40 else 3 if nl <= 64 else 2
+
+
 def gen_kernel_mfma(p, s, opt=None):
     """FP32 harmonic-basis M2L on the matrix cores (see the module header).
     Same arguments, work items, waves per workgroup and partial rows as the
@@ -423,14 +420,15 @@ def gen_kernel_mfma(p, s, opt=None):
     ms = reduced(orders(p)[nterms(s - 1):])
     nl, nm = len(ns), len(ms)
     # rows aligned to 128-byte lines: a chunk of 32 coefficients is one line
-    nlp, nmp = pad(nl, 4), pad(nm, 32 if opt["malign"] else 4)
+    nlp, nmp = pad(nl, 4), pad(nm, ROW_LINE)
     nd = pad(nterms(p), 16)
     scw = pad(p + 1, 4)
     zero = nterms(p)          # an entry of every derivative row that is zero (nd > nterms(p))
     assert zero < nd
     ng = (nl + 3) // 4
     assert 4 * ng == nlp
-    chunks, sched = mfma_schedule(p, s, opt["mch"], opt["mdist"], opt["mbalance"])
+    mch = ROW_LINE           # a chunk is one line of the rows
+    chunks, sched = mfma_schedule(p, s, mch, opt["mdist"])
     # operand groups: 16 consecutive slots of a chunk share one VGPR
     groups = []              # per group: list of (j, g, copy)
     for seq in sched:
@@ -458,6 +456,11 @@ def gen_kernel_mfma(p, s, opt=None):
     wgw = opt["wgw"]
     NT = TILE * wgw
     name = f"m2l_p{p}_s{s}_f32_hm"
+    nchunk = len(chunks)
+    assert mch == ROW_LINE
+    # two chunks in LDS where two workgroups share a CU's 160 KB
+    nbuf = 2 if mfma_waves(p, s) == 2 else 1
+    assert nbuf == 1 or nchunk >= 3
     L = []
     # operand byte offsets, two 16-bit values per word: group 2k in the low half
     words = []
@@ -468,18 +471,29 @@ def gen_kernel_mfma(p, s, opt=None):
     assert max(max(r) for r in itab) < 65536
     flat = ", ".join(str(v) for w_ in words for v in w_)
     L.append(f"static __device__ const unsigned kIdx_{name}[{len(words) * 64}] = {{{flat}}};")
-    L.append(f"__global__ __launch_bounds__({NT}, {opt['mwaves']}) void {name}(M2LArgs a)")
+    L.append(f"__global__ __launch_bounds__({NT}, {mfma_waves(p, s)}) void {name}(M2LArgs a)")
     L.append("{")
     L.append(f"    const int lane = threadIdx.x % {TILE};")
     L.append(f"    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / {TILE});")
-    L.append(f"    __shared__ float red[{nlp} * {TILE}];")
     # the operand index table, read from LDS where a group of slots needs it
     L.append(f"    __shared__ unsigned ixs[{len(words) * 64}];")
+    # per wave one or two chunks of the 64 source rows, and the sums of an
+    # item's waves when its entries are done
+    L.append(f"    __shared__ float4 area[{max(nbuf * wgw * TILE * NQ, nlp * TILE // 4)}];")
+    L.append("    float *const red = (float *)area;")
     L.append(f"    for (int k = threadIdx.x; k < {len(words) * 64}; k += {NT}) ixs[k] = kIdx_{name}[k];")
     L.append("    __syncthreads();")
     L.append("    const float *__restrict__ Mb = (const float *)a.M;")
     L.append("    const char *__restrict__ Db = (const char *)a.D;")
     L.append("    const float *__restrict__ Sb = (const float *)a.sc;")
+    # copy k of a chunk: eight rows of one line each, straight to LDS (lane i to
+    # slot i of the copy's 64); lane i takes quad (i % 8) ^ (i / 8) of row
+    # 8k + i / 8, so that the lanes' reads of one quad of their own rows fall
+    # on different banks
+    L.append(f"    const int sr = lane / {NQ}, sq = lane % {NQ};")
+    L.append(f"    const float *const Mq = Mb + 4 * (sq ^ sr);")
+    L.append(f"    float4 *const stage = area + wv * {nbuf * TILE * NQ};")
+    L.append(f"    const unsigned srd = lds_address(stage + {NQ} * lane + sq);   // quad q at srd ^ 16 q")
     L.append("    const int p0 = a.wave_ptr[blockIdx.x], p1 = a.wave_ptr[blockIdx.x + 1];")
     L.append("    for (int item = p0; item < p1; ++item) {")
     L.append("    const int4 w = a.work[item];")
@@ -489,100 +503,124 @@ def gen_kernel_mfma(p, s, opt=None):
             L.append(f"    f32x4 acc{g}_{c} = {{0.f, 0.f, 0.f, 0.f}};")
     L.append("    const int uspan = w.z - w.y;")
     L.append(f"    const int ub = w.y + uspan * wv / {wgw}, ue = w.y + uspan * (wv + 1) / {wgw};")
-    L.append("    for (int u = ub; u < ue; ++u) {")
-    if opt["fairprio"]:
-        L.append("        {")
-        L.append("            const int stage = (u - ub) * 4 / (ue - ub);")
-        L.append("            if (stage == 0) __builtin_amdgcn_s_setprio(3);")
-        L.append("            else if (stage == 1) __builtin_amdgcn_s_setprio(2);")
-        L.append("            else if (stage == 2) __builtin_amdgcn_s_setprio(1);")
-        L.append("            else __builtin_amdgcn_s_setprio(0);")
-        L.append("        }")
-    L.append("        const int cls = a.ucls[u];")
-    L.append(f"        const char *__restrict__ Dr = Db + (size_t)cls * {nd * 4};")
-    L.append(f"        const float __attribute__((address_space(4))) *sc = "
-             f"(const float __attribute__((address_space(4))) *)(Sb + (size_t)cls * {scw});")
-    L.append(f"        const float *__restrict__ Mr = Mb + (size_t)a.usrc[(size_t)u * {TILE} + lane] * {nmp};")
-    comps = "xyzw"
     # operand groups of each chunk (first global group index, count)
     gstart, gi = [], 0
     for seq in sched:
         gstart.append(gi)
         gi += (len(seq) + 15) // 16
+    ords = sorted(set(sum(m) for m in ms))
+    ng0 = (len(sched[0]) + 15) // 16
 
-    def loads(ci, mr="Mr", dr="Dr", decl=True):
-        ch, seq = chunks[ci], sched[ci]
+    def chunk_copies(src, ci, buf):
+        # row 8k + sr is the source of lane 8k + sr
+        return [f"copy_to_lds(Mq + (size_t)__builtin_amdgcn_ds_bpermute(4 * sr + {4 * (TILE // NQ) * k}, {src}) * {nmp} + "
+                f"{ROW_LINE * ci}, stage + {buf} + {TILE * k});" for k in range(NQ)]
+
+    def operands(ci, dr, decl, suf=""):
         out = []
-        kw = "const " if decl else ""
-        t4, t1 = ("float4 ", "float ") if decl else ("", "")
-        for q in sorted(set(j // 4 for j in ch)):
-            out.append(f"        {kw}{t4}v{q} = *(const float4 *)({mr} + {4 * q});")
-        for k in range((len(seq) + 15) // 16):
+        for k in range((len(sched[ci]) + 15) // 16):
             wk = gstart[ci] + k
             word = f"ixs[{(wk // 2) * 64} + lane]"
             half = f"({word} & 0xffffu)" if wk % 2 == 0 else f"({word} >> 16)"
-            out.append(f"        {kw}{t1}w{wk} = *(const float *)({dr} + {half});")
+            out.append(f"{decl}w{wk}{suf} = *(const float *)({dr} + {half});")
         return out
+
+    def scales(decl, cls, suf=""):
+        ptr = (f"const float __attribute__((address_space(4))) *sp{suf} = "
+               f"(const float __attribute__((address_space(4))) *)(Sb + (size_t){cls} * {scw});")
+        return [ptr] + [f"{decl}s{o}{suf} = sp{suf}[{o}];" for o in ords]
 
     def mfmas(ci):
         ch, seq = chunks[ci], sched[ci]
         out = []
         for j in ch:
-            out.append(f"        const float m{j} = v{j // 4}.{comps[j % 4]} * sc[{sum(ms[j])}];")
+            out.append(f"const float m{j} = v{j // 4}[{j % 4}] * s{sum(ms[j])};")
         for k in range((len(seq) + 15) // 16):
             wk = gstart[ci] + k
             for slot, (j, g, c) in enumerate(seq[16 * k:16 * k + 16]):
-                out.append(f"        acc{g}_{c} = __builtin_amdgcn_mfma_f32_4x4x1f32(w{wk}, m{j}, acc{g}_{c}, 4, {slot}, 0);")
+                out.append(f"acc{g}_{c} = __builtin_amdgcn_mfma_f32_4x4x1f32(w{wk}, m{j}, acc{g}_{c}, 4, {slot}, 0);")
         return out
 
-    def entry_ptrs(u, suf):
-        return [f"        const char *__restrict__ Dr{suf} = Db + (size_t)a.ucls[{u}] * {nd * 4};",
-                f"        const float *__restrict__ Mr{suf} = Mb + (size_t)a.usrc[(size_t)({u}) * {TILE} + lane] * {nmp};"]
+    def emit(lines, ind):
+        L.extend(" " * ind + x for x in lines)
 
-    SB = "        __builtin_amdgcn_sched_barrier(0);"
-    nchunk = len(chunks)
-    mpipe = opt["mpipe"] if nchunk > 1 else min(opt["mpipe"], 1)
-    if mpipe == 2:
-        # the first chunk's operands of entry u+1 load while entry u's last
-        # chunk multiplies (loop-carried registers); every other chunk's
-        # while the previous chunk of the same entry multiplies
-        pre = [x.replace("        ", "    ", 1) for x in loads(0, "Mr0", "Dr0", False)]
-        decl = [f"    float4 v{q};" for q in sorted(set(j // 4 for j in chunks[0]))]
-        decl += [f"    float w{gstart[0] + k};" for k in range((len(sched[0]) + 15) // 16)]
-        i_loop = L.index("    for (int u = ub; u < ue; ++u) {")
-        head = decl + ["    if (ub < ue) {"] + ["    " + x for x in entry_ptrs("ub", "0")] + ["    " + x for x in pre] + ["    }"]
-        L[i_loop:i_loop] = head
-        for ci in range(nchunk):
-            L.append(SB)
-            if ci + 1 < nchunk:
-                L.extend(loads(ci + 1))
-            else:
-                L.append("        {")
-                L.append("        const int un = u + 1 < ue ? u + 1 : u;")
-                L.extend(["    " + x for x in entry_ptrs("un", "0")])
-                L.extend(["    " + x for x in loads(0, "Mr0", "Dr0", False)])
-                L.append("        }")
-            L.extend(mfmas(ci))
-    elif mpipe == 1:
-        # the loads of chunk c+1 are issued before the multiply-adds of chunk c
-        L.extend(loads(0))
-        for ci in range(nchunk):
-            L.append(SB)
-            if ci + 1 < nchunk:
-                L.extend(loads(ci + 1))
-            L.extend(mfmas(ci))
-    else:
-        for ci in range(nchunk):
-            if opt["mbarrier"] and ci > 0:
-                # keeps the next chunk's loads from being hoisted above this
-                # point, which would hold every chunk's operands at once
-                L.append(SB)
-            L.extend(loads(ci))
-            L.extend(mfmas(ci))
-    L.append("    }")
+    SB = "__builtin_amdgcn_sched_barrier(0);"
+    CH4 = TILE * NQ          # float4s of a chunk
+    # LDS offset of chunk ci of the entry `ahead` entries on: its number among
+    # all chunks modulo the buffers (flip: this entry's first, 0 or CH4)
+    flips = nbuf == 2 and nchunk % 2 == 1
+
+    def buf(ci, ahead=0):
+        if nbuf == 1:
+            return "0"
+        k = (ci + ahead * nchunk) % 2
+        return f"({CH4} - flip)" if flips and k else "flip" if flips else str(CH4 * k)
+
+    # the first entry's sources, operands, scales and first chunks
+    emit(["int src = 0;"] + [f"float w{gstart[0] + k};" for k in range(ng0)] + [f"float s{o};" for o in ords], 4)
+    if flips:
+        emit(["int flip = 0;"], 4)
+    emit(["if (ub < ue) {"], 4)
+    emit([f"src = a.usrc[(size_t)ub * {TILE} + lane];", "const int cls = a.ucls[ub];",
+         f"const char *__restrict__ Dr = Db + (size_t)cls * {nd * 4};"] + operands(0, "Dr", "") + scales("", "cls") +
+         [SB], 8)
+    for ci in range(nbuf):
+        emit(chunk_copies("src", ci, buf(ci)), 8)
+    emit(["}"], 4)
+    emit(["for (int u = ub; u < ue; ++u) {"], 4)
+    if opt["fairprio"]:
+        emit(["{",
+              "    const int stage_ = (u - ub) * 4 / (ue - ub);",
+              "    if (stage_ == 0) __builtin_amdgcn_s_setprio(3);",
+              "    else if (stage_ == 1) __builtin_amdgcn_s_setprio(2);",
+              "    else if (stage_ == 2) __builtin_amdgcn_s_setprio(1);",
+              "    else __builtin_amdgcn_s_setprio(0);",
+              "}"], 8)
+    emit(["// the entry loaded ahead (this one again at the end of the range)",
+          "const int un = u + 1 < ue ? u + 1 : u;",
+          "const int cls = a.ucls[u], clsn = a.ucls[un];",
+          f"const char *__restrict__ Dr = Db + (size_t)cls * {nd * 4};",
+          f"const char *__restrict__ Drn = Db + (size_t)clsn * {nd * 4};"], 8)
+    # where the operands are loaded: with registers to spare all but the first
+    # chunk's one phase after their registers fall free, the next entry's in
+    # the second phase (the later ones are too short to cover the loads);
+    # otherwise each in the phase before its use
+    early = nbuf == 2 and nl < 100
+    ahead = 1 if early else nchunk - 1
+    for ci in range(nchunk):
+        # this chunk's rows are in LDS: each lane reads its own, then the copies
+        # of the chunk nbuf later are issued over them and land while this and
+        # the chunks between multiply.  Waits are spelled out: all but the
+        # NQ copies of the chunk between are done before the reads, the reads
+        # before the next copies, which are the phase's last memory operations.
+        quads = sorted(set(j // 4 for j in chunks[ci]))
+        emit([SB, f"wait_copies<{NQ * (nbuf - 1)}>();", SB] + [f"f32x4 v{q};" for q in quads], 8)
+        outs = ", ".join(f'"=&v"(v{q})' for q in quads)
+        ins = ", ".join(f'"v"((srd + 16 * {buf(ci)}) ^ {16 * (q - NQ * ci)}u)' for q in quads)
+        code = "".join(f"ds_read_b128 %{k}, %{k + len(quads)}\\n" for k in range(len(quads))) + "s_waitcnt lgkmcnt(0)"
+        emit([f'asm volatile("{code}" : {outs} : {ins} : "memory");', SB], 8)
+        if ci == 0:
+            emit([f"const int srcn = a.usrc[(size_t)un * {TILE} + lane];"], 8)
+        for cj in range(1, nchunk):
+            if ci == (min(cj - 1, 1) if early else cj - 1):
+                emit(operands(cj, "Dr", "const float "), 8)
+        if ci == ahead:
+            emit(operands(0, "Drn", "const float ", "n") + scales("const float ", "clsn", "n"), 8)
+        cn, an = (ci + nbuf) % nchunk, (ci + nbuf) // nchunk
+        emit([SB] + chunk_copies("srcn" if an else "src", cn, buf(cn, an)), 8)
+        emit(mfmas(ci), 8)
+    emit(["src = srcn;"] + [f"w{gstart[0] + k} = w{gstart[0] + k}n;" for k in range(ng0)] +
+         [f"s{o} = s{o}n;" for o in ords], 8)
+    if flips:
+        emit([f"flip = {CH4} - flip;"], 8)
+    emit(["}"], 4)
     for g in range(ng):
         for c in range(1, copies.get(g, 1)):
             L.append(f"    acc{g}_0 += acc{g}_{c};")
+    # the last copies (of an entry loaded ahead that does not come) are done
+    # before the area is used for the sums
+    L.append("    wait_copies<0>();")
+    L.append("    __syncthreads();")
     for q in range(wgw):
         last = q == wgw - 1
         L.append(f"    if (wv == {q}) {{")
@@ -627,6 +665,24 @@ def gen_file(s, fp32, opt=None, harmonic=False, mfma=False):
     if mfma:
         parts.append("typedef float f32x4 __attribute__((ext_vector_type(4)));")
         parts.append("")
+        parts.append("""// 16 bytes a lane from global memory to LDS (the lanes' data back to back from `lds`, the same for the whole wave)
+static __device__ __forceinline__ void copy_to_lds(const float *g, float4 *lds)
+{
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)g,
+                                     (__attribute__((address_space(3))) void *)lds, 16, 0, 0);
+}
+static __device__ __forceinline__ unsigned lds_address(const float4 *p)
+{
+    return (unsigned)(size_t)(const __attribute__((address_space(3))) void *)p;
+}
+// s_waitcnt vmcnt(N): all but the wave's last N copies and loads are done
+template <int N>
+static __device__ __forceinline__ void wait_copies()
+{
+    static_assert(N < 16, "vmcnt's low bits");
+    __builtin_amdgcn_s_waitcnt(0x0f70 | N);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}""")
     metas = []
     for p in range(s + 1, P_MAX + 1):
         code, meta = gen_kernel_mfma(p, s, opt) if mfma else gen_kernel(p, s, fp32, opt, harmonic)

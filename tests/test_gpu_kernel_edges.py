@@ -13,7 +13,7 @@ if not torch.cuda.is_available():  # pragma: no cover
 
 from paper_2005_12351_amd import fmm  # noqa: E402
 from paper_2005_12351_amd import workloads as W  # noqa: E402
-from tests.gpu_helpers import to_dev, within  # noqa: E402
+from tests.gpu_helpers import PHI_FLOOR, to_dev, within  # noqa: E402
 
 FP64, MIXED = fmm.FMM_PREC_FP64, fmm.FMM_PREC_MIXED
 
@@ -50,5 +50,29 @@ def test_derivatives_tiles(orc, ctx, order, n, ncrit, kind):
         torch.cuda.synchronize()
         # pooled and per target: the bounds of the FP64 derivative parity test
         ok &= within(d.cpu().numpy(), ot.fmm_derivs(w.order, w.moments, p, K), FP64, f"order {K}", (1e-10, 1e-12))
+    t.close()
+    assert ok
+
+
+# the matrix-core M2L over its row chunks (one to four lines), LDS buffers
+# (odd and even chunk counts of two buffers, one buffer) and pieces with fewer
+# entries than waves; ncrit 4 at n = 700 gives pieces of a few hundred entries
+@pytest.mark.parametrize("p,s", [(1, 0), (4, 0), (5, 0), (6, 1), (7, 2), (8, 0), (8, 1), (8, 3), (9, 1), (10, 0), (10, 1),
+                                 (10, 2), (10, 3)])
+@pytest.mark.parametrize("n,ncrit", [(150, 16), (700, 4)])
+def test_matrix_core_m2l_chunks(orc, ctx, p, s, n, ncrit):
+    w = _workload(4200 + 10 * p + s, s, n, "uniform", p, ncrit)
+    print(f"[mfma m2l] p={p} s={s} n={n}", flush=True)
+    ctx.set_m2l_engine(fmm.FMM_M2L_ENGINE_MFMA)
+    try:
+        t = fmm.Tree(ctx, to_dev(w.pos), ncrit, w.theta)
+        phi, E = t.run(s, to_dev(w.moments), p, MIXED)
+        torch.cuda.synchronize()
+    finally:
+        ctx.set_m2l_engine(fmm.FMM_M2L_ENGINE_AUTO)
+    assert t.info()["n_m2l"] > 0
+    ophi, oE = orc.Tree(w.pos, ncrit, w.theta).fmm(w.order, w.moments, p)[:2]
+    ok = within(E.cpu().numpy(), oE, MIXED, "E")
+    ok &= within(phi.cpu().numpy(), ophi, MIXED, "phi", floor=PHI_FLOOR)
     t.close()
     assert ok
