@@ -48,6 +48,15 @@ consecutive multiply-add slots (j, g), gathered per lane from the class's
 derivative row through a fixed index table (an index past the tensor reads a
 zero for outputs a slot does not reach).  Per slot: 64 targets x 4 outputs
 in one instruction, twice the FP32 multiply-add rate of the vector unit.
+The rows come through LDS: a lane that loads its own row touches 64 cache
+lines an instruction, which kept the address units busier than the matrix
+pipe.  Eight lanes that share a row's 128-byte line copy it straight to LDS,
+swizzled so that each lane then reads its own row without bank conflicts; the
+copies of later chunks land while the current one multiplies, and need no
+registers.  What bounds it now is the issue of the 4x4x1 instruction (6.5 to
+6.9 ns each per SIMD, 4.8 in a loop of nothing else).  2x10^6 quadrupoles,
+theta 0.5, p 10: 1.07 -> 0.81 ms a launch; 100k dipoles, theta 0.3, p 10:
+0.384 -> 0.373 ms.
 
 Usage: python gen_m2l.py OUTDIR  -> OUTDIR/m2l_s{0,1,2}_{f32,f64}[_h].hip, m2l_s{0,1,2}_f32_hm.hip
 """
