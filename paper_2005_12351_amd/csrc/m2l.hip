@@ -2,6 +2,7 @@
 // Eq. 7-8): the derivative tensor of every translation class, the launch of
 // the generated contraction kernels, and the FP64 combination of their
 // partial rows into the local expansions.
+#include <algorithm>
 #include <cmath>
 
 #include "fmm_internal.h"
@@ -102,123 +103,92 @@ hipError_t launch_m2l(fmm_tree *t, hipStream_t s)
     return v.launch(a, wk.nwaves, s);
 }
 
-// L~ of every cell (FP64): the sum, in chunk order, of the partial rows of the
-// cell's tile slot (each output block of a tile has its own chunks), or zero
-// for a cell without M2L sources; so the locals need no separate clearing.
-// The loads of eight chunks are issued before their fixed-order sum.
-// Harmonic basis: the rows hold the components with n_z <= 1; another
-// component (a, b, 2j + r) is (-1)^j sum_i C(j,i) of the summed components
-// (a + 2i, b + 2(j - i), r), the identity the locals inherit from D (their
-// truncation |m| <= p - |n| is the same for every component of one order).
+// L~ of every cell (FP64): the sum of the partial rows of the cell's tile slot
+// (each output block of a tile has its own chunks), or zero for a cell without
+// M2L sources; so the locals need no separate clearing.  nl components a cell
+// (harmonic basis: those with n_z <= 1, as the rows and the locals hold them).
+// What bounds it is the latency of a thread's chain of loads: a tree of few
+// tiles is cut into hundreds of row sets a tile (1000 charges: 310 for the one
+// tile).  PARTS threads share a sum, each taking every PARTS-th row set in
+// batches of eight loads; the host picks PARTS from the row sets a tile has.
 struct BlockBounds {
     int lo[17];
     int nb;
 };
 
-template <typename T>
-__device__ __forceinline__ double sum_partials(int n, int tile, int lane, int nlp, const BlockBounds &bb,
-                                               const int32_t *__restrict__ chunk0,
-                                               const int32_t *__restrict__ nchunk, const T *__restrict__ part)
+template <typename T, int PARTS>
+__global__ __launch_bounds__(256) void m2l_combine_kernel(int ncells, int nl, int nlp, BlockBounds bb,
+                                                          const int32_t *__restrict__ cell_slot,
+                                                          const int32_t *__restrict__ chunk0,
+                                                          const int32_t *__restrict__ nchunk,
+                                                          const T *__restrict__ part, double *__restrict__ L)
 {
-    int b = 0;
-    while (b + 1 < bb.nb && n >= bb.lo[b + 1]) ++b;
-    const int c0 = chunk0[tile * bb.nb + b], nc = nchunk[tile * bb.nb + b];
-    const T *p = part + ((size_t)c0 * kTileW + lane) * nlp + n;
-    const size_t stride = (size_t)kTileW * nlp;
-    double acc = 0.0;
-    int k = 0;
-    for (; k + 8 <= nc; k += 8) {
-        T v[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] = p[(size_t)(k + q) * stride];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) acc += (double)v[q];
-    }
-    for (; k < nc; ++k) acc += (double)p[(size_t)k * stride];
-    return acc;
-}
-
-template <typename T>
-__global__ void m2l_combine_kernel(int ncells, int nl, int nlp, BlockBounds bb, const int32_t *__restrict__ cell_slot,
-                                   const int32_t *__restrict__ chunk0, const int32_t *__restrict__ nchunk,
-                                   const T *__restrict__ part, double *__restrict__ L)
-{
-    const size_t id = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-    if (id >= (size_t)ncells * nl) return;
+    constexpr int kItems = 256 / PARTS;   // sums of the workgroup, adjacent threads on adjacent components
+    const int item = threadIdx.x % kItems, k0 = threadIdx.x / kItems;
+    const size_t id = blockIdx.x * (size_t)kItems + item, tot = (size_t)ncells * nl;
     const int cell = (int)(id / nl), n = (int)(id % nl);
-    const int slot = cell_slot[cell];
+    const int slot = id < tot ? cell_slot[cell] : -1;
     double acc = 0.0;
-    if (slot >= 0) acc = sum_partials(n, slot / kTileW, slot % kTileW, nlp, bb, chunk0, nchunk, part);
-    L[(size_t)cell * nl + n] = acc;
-}
-
-// Harmonic basis, kHarmCells cells per workgroup: the summed components with
-// n_z <= 1 go to LDS, then every component of the cells' rows is written
-// (full rows, nl per cell) or, when the locals are kept reduced (nl == 0),
-// just those components (nlh per cell).
-constexpr int kHarmCells = 4;
-template <typename T>
-__global__ __launch_bounds__(256) void m2l_combine_h_kernel(int ncells, int nl, int nlh, int nlp, BlockBounds bb,
-                                                            const int32_t *__restrict__ cell_slot,
-                                                            const int32_t *__restrict__ chunk0,
-                                                            const int32_t *__restrict__ nchunk,
-                                                            const T *__restrict__ part, double *__restrict__ L)
-{
-    __shared__ double red[kHarmCells][hterms(FMM_P_MAX)];
-    const int c0 = blockIdx.x * kHarmCells;
-    for (int it = threadIdx.x; it < kHarmCells * nlh; it += blockDim.x) {
-        const int cc = it / nlh, h = it % nlh, cell = c0 + cc;
-        double v = 0.0;
-        const int slot = cell < ncells ? cell_slot[cell] : -1;
-        if (slot >= 0) v = sum_partials(h, slot / kTileW, slot % kTileW, nlp, bb, chunk0, nchunk, part);
-        red[cc][h] = v;
-        if (nl == 0 && cell < ncells) L[(size_t)cell * nlh + h] = v;
-    }
-    if (nl == 0) return;
-    __syncthreads();
-    for (int it = threadIdx.x; it < kHarmCells * nl; it += blockDim.x) {
-        const int cc = it / nl, n = it % nl, cell = c0 + cc;
-        if (cell >= ncells) break;
-        const MultiIndex nn = k_mi.v[n];
-        const int j = nn.z / 2, r = nn.z & 1;
-        double acc = 0.0, c = 1.0;   // c = C(j, i)
-        for (int i = 0; i <= j; ++i) {
-            acc = fma(c, red[cc][hindex(nn.x + 2 * i, nn.y + 2 * (j - i), r)], acc);
-            c = c * (j - i) / (i + 1);
+    if (slot >= 0) {
+        const int tile = slot / kTileW, lane = slot % kTileW;
+        int b = 0;
+        while (b + 1 < bb.nb && n >= bb.lo[b + 1]) ++b;
+        const int c0 = chunk0[tile * bb.nb + b], nc = nchunk[tile * bb.nb + b];
+        const T *p = part + ((size_t)c0 * kTileW + lane) * nlp + n;
+        const size_t stride = (size_t)kTileW * nlp;
+        int k = k0;
+        for (; k + 7 * PARTS < nc; k += 8 * PARTS) {
+            T v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = p[(size_t)(k + q * PARTS) * stride];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) acc += (double)v[q];
         }
-        L[(size_t)cell * nl + n] = (j & 1) ? -acc : acc;
+        for (; k < nc; k += PARTS) acc += (double)p[(size_t)k * stride];
     }
+    if constexpr (PARTS > 1) {
+        __shared__ double red[256];
+        red[threadIdx.x] = acc;
+        __syncthreads();
+        if (k0 > 0) return;
+#pragma unroll
+        for (int q = 1; q < PARTS; ++q) acc += red[q * kItems + item];
+    }
+    if (id < tot) L[id] = acc;
 }
 
 hipError_t launch_m2l_combine(fmm_tree *t, hipStream_t s)
 {
-    const int nl = nterms(t->p - t->order);
     const int64_t nc = t->ht.ncells();
     const bool f32 = t->prec == FMM_PREC_MIXED, harm = t->basis == FMM_M2L_HARMONIC;
+    const int nl = harm ? hterms(t->p - t->order) : nterms(t->p - t->order);
     M2LVariant v;
     if (!m2l_lookup(t->p, t->order, f32, harm, &v, t->mfma)) return hipErrorInvalidValue;
     BlockBounds bb;
     for (int i = 0; i < 17; ++i) bb.lo[i] = v.blo[i];
     bb.nb = v.nblocks;
-    if (harm) {
-        const unsigned g = (unsigned)((nc + kHarmCells - 1) / kHarmCells);
-        const int nlh = hterms(t->p - t->order);
-        // the locals stay reduced (nl = 0 asks for the n_z <= 1 part only)
-#define COMBINE_H(T)                                                                                            \
-    hipLaunchKernelGGL(m2l_combine_h_kernel<T>, dim3(g), dim3(256), 0, s, (int)nc, 0, nlh, v.nl_pad, bb,         \
+    // row sets a tile's sum has on average.  One thread a sum while two
+    // batches of loads take them (100k dipoles, 8 sets: 10.7 us, 11.5 before);
+    // above that the chain costs more than the LDS sum of the parts: 1000
+    // charges (310 sets) 21.3 -> 8.0 us, 3001 Plummer quadrupoles 36 -> 11.4,
+    // 10 007 dipoles (57) 10.3 -> 9.4.
+    const int64_t sums = (int64_t)std::max(1, t->tiling.ntiles) * v.nblocks;
+    const int64_t sets = t->m2lwork.nrows / kTileW / sums;
+    const int parts = sets > 96 ? 32 : sets > 16 ? 8 : 1;
+    const unsigned g = (unsigned)(((size_t)nc * nl + 256 / parts - 1) / (256 / parts));
+#define COMBINE(T, P)                                                                                           \
+    hipLaunchKernelGGL((m2l_combine_kernel<T, P>), dim3(g), dim3(256), 0, s, (int)nc, nl, v.nl_pad, bb,          \
                        t->d_cell_slot, t->d_tile_chunk0, t->d_tile_nchunk, (const T *)t->d_part, t->d_L64)
-        if (f32) COMBINE_H(float);
-        else COMBINE_H(double);
-#undef COMBINE_H
-        return hipGetLastError();
+#define COMBINE_T(T)                   \
+    if (parts == 32) COMBINE(T, 32);   \
+    else if (parts == 8) COMBINE(T, 8); \
+    else COMBINE(T, 1)
+    if (f32) {
+        COMBINE_T(float);
+    } else {
+        COMBINE_T(double);
     }
-    const size_t tot = (size_t)nc * nl;
-    const unsigned g = (unsigned)((tot + 255) / 256);
-#define COMBINE(T)                                                                                              \
-    hipLaunchKernelGGL(m2l_combine_kernel<T>, dim3(g), dim3(256), 0, s, (int)nc, nl, v.nl_pad, bb,              \
-                       t->d_cell_slot, t->d_tile_chunk0, t->d_tile_nchunk, (const T *)t->d_part, t->d_L64)
-    if (f32) COMBINE(float);
-    else COMBINE(double);
+#undef COMBINE_T
 #undef COMBINE
     return hipGetLastError();
 }

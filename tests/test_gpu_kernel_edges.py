@@ -76,3 +76,26 @@ def test_matrix_core_m2l_chunks(orc, ctx, p, s, n, ncrit):
     ok &= within(phi.cpu().numpy(), ophi, MIXED, "phi", floor=PHI_FLOOR)
     t.close()
     assert ok
+
+
+# the combine's split of a tile's row sets: one tile of hundreds of sets (32
+# threads a sum), a few tiles (8), many (1); fewer cells than a workgroup holds
+@pytest.mark.parametrize("n,ncrit,p,s", [(100, 4, 1, 0), (1000, 64, 4, 0), (1000, 64, 6, 1), (3000, 16, 5, 2),
+                                         (8000, 8, 4, 1)])
+@pytest.mark.parametrize("prec,basis", [(FP64, fmm.FMM_M2L_HARMONIC), (MIXED, fmm.FMM_M2L_HARMONIC),
+                                        (FP64, fmm.FMM_M2L_FULL)])
+def test_combine_parts(orc, ctx, n, ncrit, p, s, prec, basis):
+    w = _workload(4300 + n + p, s, n, "uniform", p, ncrit)
+    print(f"[combine] n={n} ncrit={ncrit} p={p} s={s} precision={prec} basis={basis}", flush=True)
+    ctx.set_m2l_basis(basis)
+    try:
+        t = fmm.Tree(ctx, to_dev(w.pos), ncrit, w.theta)
+        phi, E = t.run(s, to_dev(w.moments), p, prec)
+        torch.cuda.synchronize()
+    finally:
+        ctx.set_m2l_basis(fmm.FMM_M2L_HARMONIC)
+    ophi, oE = orc.Tree(w.pos, ncrit, w.theta).fmm(w.order, w.moments, p)[:2]
+    ok = within(E.cpu().numpy(), oE, prec, "E")
+    ok &= within(phi.cpu().numpy(), ophi, prec, "phi", floor=PHI_FLOOR)
+    t.close()
+    assert ok
