@@ -172,7 +172,7 @@ __global__ __launch_bounds__(64) void bh_kernel(BHArgs a)
                                 p2p_pair_oct_f32(rx, ry, rz, inv, m4[0], m4[1], m4[2], m4[3], bp, bx, by, bz);
                                 if constexpr (GRAD) p2p_pair_grad_oct_f32(rx, ry, rz, inv, m4[0], m4[1], m4[2], m4[3], bg);
                             } else {
-                                p2p_pair_f32<S>(rx, ry, rz, inv, m4[0], m4[1], bp, bx, by, bz);
+                                p2p_pair_f32<S>(rx, ry, rz, r2, inv, m4[0], m4[1], bp, bx, by, bz);
                                 if constexpr (GRAD) p2p_pair_grad_f32<S>(rx, ry, rz, inv, m4[0], m4[1], bg);
                             }
                         }
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(64) void bh_kernel(BHArgs a)
 #pragma unroll
                         for (int q = 0; q < S; ++q) sphi *= ir;
                         const double sfld = sphi * ir;
-                        ph += (double)bp * sphi;
+                        ph += (double)bp * (p2p_phi_scale(S) * sphi);
                         ex += (double)bx * sfld;
                         ey += (double)by * sfld;
                         ez += (double)bz * sfld;

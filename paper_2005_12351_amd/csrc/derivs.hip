@@ -255,7 +255,6 @@ __global__ __launch_bounds__(kDT) void derivs_kernel(DerivArgs d)
     constexpr int kArea = kCube > kStage ? (kCube > kRed ? kCube : kRed) : (kStage > kRed ? kStage : kRed);
     __shared__ double area[kArea];
     __shared__ int wstart[kPList], wfirst[kPList];
-    __shared__ float4 wgeo[kPList];
     __shared__ int sh[kPT / 64];
     __shared__ int wself;
     const P2PArgs &a = d.near;
@@ -341,7 +340,7 @@ __global__ __launch_bounds__(kDT) void derivs_kernel(DerivArgs d)
             __syncthreads();
             if (tid == 0) wself = -1;
             __syncthreads();
-            const int nsw = p2p_window(a, cb, b, w0, nw, wstart, wfirst, wgeo, &wself, sh);
+            const int nsw = p2p_window(a, b, w0, nw, wstart, wfirst, &wself, sh);
             for (int c0 = 0; c0 < nsw; c0 += kDChunk) {
                 const int nc = min(kDChunk, nsw - c0);
                 __syncthreads();

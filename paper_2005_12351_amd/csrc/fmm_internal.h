@@ -40,9 +40,9 @@ __host__ __device__ constexpr int mask_width(int m)
 __host__ __device__ constexpr int mask_min_order(int m) { return m & 1 ? 0 : (m & 2 ? 1 : (m & 4 ? 2 : 3)); }
 __host__ __device__ constexpr bool mask_single(int m) { return m == 1 || m == 2 || m == 4 || m == 8; }
 // FP32 moments per particle, in float4 groups: one order of 0..2: 8 floats
-// (q | mu | six Q and the trace); octupoles alone: 16 ([O xxx xxy xxz xyy]
+// (q | mu | six Q, the trace and -1.5 times it); octupoles alone: 16 ([O xxx xxy xxz xyy]
 // [xyz xzz yyy yyz] [yzz zzz t_x t_y] [t_z 0 0 0], t the trace vector
-// t_k = sum_i O_iik); several orders: 12 ([q mu] [xx xy xz yy] [yz zz tr 0],
+// t_k = sum_i O_iik); several orders: 12 ([q mu] [xx xy xz yy] [yz zz tr -1.5tr],
 // absent parts 0), followed by the 16 of the octupole block when that order
 // is present
 __host__ __device__ constexpr int m32_width(int m)

@@ -110,7 +110,10 @@ __device__ __forceinline__ void sort_moments(size_t i, int mask, const double *_
         oct(r, 0);
     } else if (mask_single(mask)) {
         for (int k = 0; k < w; ++k) v[k] = (float)r[k];
-        if (w == 6) v[6] = (float)(r[0] + r[3] + r[5]);
+        if (w == 6) {
+            v[6] = (float)(r[0] + r[3] + r[5]);
+            v[7] = -1.5f * v[6];
+        }
     } else {
         int off = 0;
         if (mask & 1) v[0] = (float)r[off++];
@@ -123,6 +126,7 @@ __device__ __forceinline__ void sort_moments(size_t i, int mask, const double *_
         if (mask & 4) {
             for (int k = 0; k < 6; ++k) v[4 + k] = (float)r[off + k];
             v[10] = (float)(r[off] + r[off + 3] + r[off + 5]);
+            v[11] = -1.5f * v[10];
             off += 6;
         }
         if (mask & 8) oct(r + off, 12);

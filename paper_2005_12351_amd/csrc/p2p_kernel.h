@@ -77,25 +77,18 @@ __device__ __forceinline__ int p2p_block_scan(int v, int *sh, int *tot)
 }
 
 // Window of up to kPList list entries: start offset of each entry's particles
-// within the window, first particle, source geometry relative to the target
-// leaf (centre difference in units of r_b, and r_A / r_b), and the window
-// offset of the target leaf's own entry (-1 if absent).  The slots of
-// wstart past the window's entries hold INT_MAX (see p2p_entry).  Returns
-// the number of staged sources of the window.
-static __device__ int p2p_window(const P2PArgs &a, const DevCell &cb, int b, int w0, int nw, int *wstart, int *wfirst,
-                          float4 *wgeo, int *wself, int *sh)
+// within the window, first particle, and the window offset of the target
+// leaf's own entry (-1 if absent).  The slots of wstart past the window's
+// entries hold INT_MAX (see p2p_entry).  Returns the number of staged sources
+// of the window.
+static __device__ int p2p_window(const P2PArgs &a, int b, int w0, int nw, int *wstart, int *wfirst, int *wself, int *sh)
 {
     const int q = threadIdx.x;
     int cnt = 0;
     if (q < nw) {
         const int A = a.src[w0 + q];
-        const DevCell c = a.cells[A];
-        cnt = c.count;
-        wfirst[q] = c.first;
-        const double rho = ldexp(1.0, cb.level - c.level);
-        wgeo[q] = make_float4((float)((double)(2 * c.ix + 1) * rho - (double)(2 * cb.ix + 1)),
-                              (float)((double)(2 * c.iy + 1) * rho - (double)(2 * cb.iy + 1)),
-                              (float)((double)(2 * c.iz + 1) * rho - (double)(2 * cb.iz + 1)), (float)rho);
+        cnt = a.cells[A].count;
+        wfirst[q] = a.cells[A].first;
         if (A == b) *wself = -2 - q;   // marks the entry; replaced by its start below
     }
     int tot;
@@ -125,14 +118,14 @@ __device__ __forceinline__ int p2p_entry(const int *wstart, int nw, int j)
 // its own sums (the orders scale differently with the leaf radius); mv is the
 // particle's staged FP32 block (m32_width)
 template <int MASK, int NV>
-__device__ __forceinline__ void p2p_pair_mixed(float rx, float ry, float rz, float inv, const float4 (&mv)[NV],
+__device__ __forceinline__ void p2p_pair_mixed(float rx, float ry, float rz, float r2, float inv, const float4 (&mv)[NV],
                                                float (&bp)[4], float (&bx)[4], float (&by)[4], float (&bz)[4])
 {
     const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
-    if constexpr (MASK & 1) p2p_pair_f32<0>(rx, ry, rz, inv, mv[0], z4, bp[0], bx[0], by[0], bz[0]);
+    if constexpr (MASK & 1) p2p_pair_f32<0>(rx, ry, rz, r2, inv, mv[0], z4, bp[0], bx[0], by[0], bz[0]);
     if constexpr (MASK & 2)
-        p2p_pair_f32<1>(rx, ry, rz, inv, make_float4(mv[0].y, mv[0].z, mv[0].w, 0.f), z4, bp[1], bx[1], by[1], bz[1]);
-    if constexpr (MASK & 4) p2p_pair_f32<2>(rx, ry, rz, inv, mv[1], mv[2], bp[2], bx[2], by[2], bz[2]);
+        p2p_pair_f32<1>(rx, ry, rz, r2, inv, make_float4(mv[0].y, mv[0].z, mv[0].w, 0.f), z4, bp[1], bx[1], by[1], bz[1]);
+    if constexpr (MASK & 4) p2p_pair_f32<2>(rx, ry, rz, r2, inv, mv[1], mv[2], bp[2], bx[2], by[2], bz[2]);
     if constexpr (MASK & 8) p2p_pair_oct_f32(rx, ry, rz, inv, mv[3], mv[4], mv[5], mv[6], bp[3], bx[3], by[3], bz[3]);
 }
 
@@ -161,9 +154,14 @@ __device__ __forceinline__ void p2p_pair_grad_mixed(float rx, float ry, float rz
 }
 
 // GRAD: the six field-gradient components instead of phi and E (sums of
-// order k scaled by r_b^-(k+3)), written to near_g.  The launch bound asks
-// for five resident workgroups per CU, which fits the dipole kernel in 82
-// VGPRs without spills (114 unbounded).
+// order k scaled by r_b^-(k+3)), written to near_g.  What bounds it is the
+// issue of the pair terms (25 vector operations for a dipole, 41 for a
+// quadrupole; the staging and idle lanes bring a dipole pair to 30.6).  The
+// launch bound asks for five resident workgroups per CU; the dipole kernel
+// takes 78 VGPRs and 26.6 KB of LDS, so six are resident: 100k dipoles, theta
+// 0.3: 255 -> 238 us from the sixth; 2x10^6 quadrupoles 3.73 -> 3.38 ms from
+// 46 operations a pair to 41.  (Staging whole entries by groups of lanes
+// instead of searching for each source's entry measured the same.)
 template <int MASK, bool GRAD>
 __global__ __launch_bounds__(kPT, 5) void p2p_f32_kernel(P2PArgs a)
 {
@@ -182,7 +180,6 @@ __global__ __launch_bounds__(kPT, 5) void p2p_f32_kernel(P2PArgs a)
     static_assert(NO * kPT * sizeof(double) <= sizeof(P2PStaged<NV>) * CH, "reduction buffer exceeds the staging area");
     double (*const red)[kPT] = reinterpret_cast<double (*)[kPT]>(sst);
     __shared__ int wstart[kPList], wfirst[kPList];
-    __shared__ float4 wgeo[kPList];
     __shared__ int sh[kPT / 64];
     __shared__ int wself;
     const int tid = threadIdx.x;
@@ -202,7 +199,7 @@ __global__ __launch_bounds__(kPT, 5) void p2p_f32_kernel(P2PArgs a)
     sfld[2] = sphi[3];
     sfld[3] = sphi[3] * irb;
     // scale of output component c of the order-k sums
-    auto scale = [&](int c, int k) { return GRAD ? sfld[k] * irb : (c == 0 ? sphi[k] : sfld[k]); };
+    auto scale = [&](int c, int k) { return GRAD ? sfld[k] * irb : (c == 0 ? p2p_phi_scale(k) * sphi[k] : sfld[k]); };
     double zb[3];
     {
         const double r = ldexp(1.0, kMaxLevel - cb.level);
@@ -235,7 +232,7 @@ __global__ __launch_bounds__(kPT, 5) void p2p_f32_kernel(P2PArgs a)
             __syncthreads();
             if (tid == 0) wself = -1;
             __syncthreads();
-            const int nsw = p2p_window(a, cb, b, w0, nw, wstart, wfirst, wgeo, &wself, sh);
+            const int nsw = p2p_window(a, b, w0, nw, wstart, wfirst, &wself, sh);
             // chunks are a multiple of the slice count long, and the last one
             // is padded with zero sources far away (their terms are exactly
             // zero), so every slice takes the same number of sources and the
@@ -306,10 +303,10 @@ __global__ __launch_bounds__(kPT, 5) void p2p_f32_kernel(P2PArgs a)
                             if constexpr (S == 3)
                                 p2p_pair_oct_f32(rx, ry, rz, inv, mv[0], mv[1], mv[2], mv[3], bs[0][3], bs[1][3], bs[2][3],
                                                  bs[3][3]);
-                            else p2p_pair_f32<S>(rx, ry, rz, inv, mv[0], mv[NV > 1 ? 1 : 0], bs[0][S], bs[1][S], bs[2][S],
+                            else p2p_pair_f32<S>(rx, ry, rz, r2, inv, mv[0], mv[NV > 1 ? 1 : 0], bs[0][S], bs[1][S], bs[2][S],
                                                  bs[3][S]);
                         } else {
-                            p2p_pair_mixed<MASK, NV>(rx, ry, rz, inv, mv, bs[0], bs[1], bs[2], bs[3]);
+                            p2p_pair_mixed<MASK, NV>(rx, ry, rz, r2, inv, mv, bs[0], bs[1], bs[2], bs[3]);
                         }
                     }
                     };
@@ -350,7 +347,10 @@ __global__ __launch_bounds__(kPT, 5) void p2p_f32_kernel(P2PArgs a)
     }
 }
 
-// (five resident workgroups per CU, as the FP32 kernel)
+// (at least five resident workgroups per CU, as the FP32 kernel; an FP64
+// operation issues every 5.4 cycles with four waves a SIMD, 7.4 with two.
+// 100k, theta 0.3: dipoles 450 -> 387 us, charges 352 -> 290, their gradient
+// 445 -> 392, from pair terms with fewer operations and a shorter 1/sqrt)
 template <int MASK, bool GRAD>
 __global__ __launch_bounds__(kPT, 5) void p2p_f64_kernel(P2PArgs a)
 {
@@ -358,7 +358,6 @@ __global__ __launch_bounds__(kPT, 5) void p2p_f64_kernel(P2PArgs a)
     constexpr int NO = GRAD ? 6 : 4;
     __shared__ double sx[kPChunk64], sy[kPChunk64], sz[kPChunk64], sm[W][kPChunk64];
     __shared__ int wstart[kPList], wfirst[kPList];
-    __shared__ float4 wgeo[kPList];
     __shared__ double red[NO][kPT];
     __shared__ int sh[kPT / 64];
     __shared__ int wself;
@@ -391,7 +390,7 @@ __global__ __launch_bounds__(kPT, 5) void p2p_f64_kernel(P2PArgs a)
             __syncthreads();
             if (tid == 0) wself = -1;
             __syncthreads();
-            const int nsw = p2p_window(a, cb, b, w0, nw, wstart, wfirst, wgeo, &wself, sh);
+            const int nsw = p2p_window(a, b, w0, nw, wstart, wfirst, &wself, sh);
             // as in the FP32 kernel: chunks a multiple of the slice count long,
             // the last padded with zero sources 10^4 leaf radii away, so all
             // slices take the same number of sources

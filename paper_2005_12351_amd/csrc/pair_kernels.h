@@ -7,9 +7,12 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+// FP32 (r2 = |r|^2, inv = 1/|r|).  The quadrupole adds twice its potential:
+// the sum is halved where it is scaled (p2p_phi_scale), which rounds alike
+// and takes one operation a pair less.  m1 = (yz, zz, tr Q, -1.5 tr Q).
 template <int S>
-__device__ __forceinline__ void p2p_pair_f32(float rx, float ry, float rz, float inv, const float4 &m0, const float4 &m1,
-                                             float &ph, float &ex, float &ey, float &ez)
+__device__ __forceinline__ void p2p_pair_f32(float rx, float ry, float rz, float r2, float inv, const float4 &m0,
+                                             const float4 &m1, float &ph, float &ex, float &ey, float &ez)
 {
     const float inv2 = inv * inv;
     const float inv3 = inv * inv2;
@@ -27,60 +30,68 @@ __device__ __forceinline__ void p2p_pair_f32(float rx, float ry, float rz, float
         ey = __builtin_fmaf(inv3, __builtin_fmaf(t1, ry, -m0.y), ey);
         ez = __builtin_fmaf(inv3, __builtin_fmaf(t1, rz, -m0.z), ez);
     } else {
-        // m0 = (xx, xy, xz, yy), m1 = (yz, zz, tr, -)
+        // m0 = (xx, xy, xz, yy)
         const float qx = __builtin_fmaf(m0.x, rx, __builtin_fmaf(m0.y, ry, m0.z * rz));
         const float qy = __builtin_fmaf(m0.y, rx, __builtin_fmaf(m0.w, ry, m1.x * rz));
         const float qz = __builtin_fmaf(m0.z, rx, __builtin_fmaf(m1.x, ry, m1.y * rz));
         const float rqr = __builtin_fmaf(rx, qx, __builtin_fmaf(ry, qy, rz * qz));
         const float inv5 = inv3 * inv2;
-        const float r2 = rx * rx + ry * ry + rz * rz;
-        ph = __builtin_fmaf(0.5f * inv5, __builtin_fmaf(3.0f, rqr, -r2 * m1.z), ph);
-        const float a = __builtin_fmaf(7.5f * rqr, inv2, -1.5f * m1.z);
+        ph = __builtin_fmaf(inv5, __builtin_fmaf(3.0f, rqr, -r2 * m1.z), ph);
+        const float a = __builtin_fmaf(7.5f * rqr, inv2, m1.w);
         ex = __builtin_fmaf(inv5, __builtin_fmaf(a, rx, -3.0f * qx), ex);
         ey = __builtin_fmaf(inv5, __builtin_fmaf(a, ry, -3.0f * qy), ey);
         ez = __builtin_fmaf(inv5, __builtin_fmaf(a, rz, -3.0f * qz), ez);
     }
+}
+// factor of the FP32 potential sums of order k
+__host__ __device__ constexpr double p2p_phi_scale(int k) { return k == 2 ? 0.5 : 1.0; }
+
+// 1/sqrt(r2) to FP64: the hardware estimate y (relative error e/2 up to
+// 5.2e-8, measured over 2^20 values) and one step of third order,
+// y (1 + e/2 + 3 e^2/8) with e = 1 - r2 y^2; 1.4e-16 at most after it, against
+// 2.4e-16 for two Newton steps, which take two operations more.
+__device__ __forceinline__ double rsq_f64(double r2)
+{
+    const double y = __builtin_amdgcn_rsq(r2);
+    const double e = __builtin_fma(-(r2 * y), y, 1.0);
+    return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
 }
 
 template <int S>
 __device__ __forceinline__ void p2p_pair_f64(double rx, double ry, double rz, const double *m, double &ph, double &ex,
                                              double &ey, double &ez)
 {
-    const double r2 = rx * rx + ry * ry + rz * rz;
-    // hardware reciprocal square root estimate, two Newton steps
-    double inv = __builtin_amdgcn_rsq(r2);
-    const double hr = 0.5 * r2;
-    inv = inv * __builtin_fma(-hr * inv, inv, 1.5);
-    inv = inv * __builtin_fma(-hr * inv, inv, 1.5);
+    const double inv = rsq_f64(rx * rx + ry * ry + rz * rz);
     const double inv2 = inv * inv;
     const double inv3 = inv * inv2;
     if (S == 0) {
-        ph += m[0] * inv;
-        ex += m[0] * rx * inv3;
-        ey += m[0] * ry * inv3;
-        ez += m[0] * rz * inv3;
+        const double q3 = m[0] * inv3;
+        ph = __builtin_fma(m[0], inv, ph);
+        ex = __builtin_fma(q3, rx, ex);
+        ey = __builtin_fma(q3, ry, ey);
+        ez = __builtin_fma(q3, rz, ez);
     } else if (S == 1) {
+        // E = (3 (mu.r) r / r^2 - mu) / r^3
         const double mr = m[0] * rx + m[1] * ry + m[2] * rz;
-        const double inv5 = inv3 * inv2;
-        ph += mr * inv3;
-        ex += (3.0 * mr * rx - r2 * m[0]) * inv5;
-        ey += (3.0 * mr * ry - r2 * m[1]) * inv5;
-        ez += (3.0 * mr * rz - r2 * m[2]) * inv5;
+        ph = __builtin_fma(mr, inv3, ph);
+        const double t = 3.0 * mr * inv2;
+        ex = __builtin_fma(inv3, __builtin_fma(t, rx, -m[0]), ex);
+        ey = __builtin_fma(inv3, __builtin_fma(t, ry, -m[1]), ey);
+        ez = __builtin_fma(inv3, __builtin_fma(t, rz, -m[2]), ez);
     } else {
+        // E = (a r - 3 Q r) / r^5, a = 7.5 r.Q.r / r^2 - 1.5 tr Q;
+        // phi = 0.5 (3 r.Q.r / r^2 - tr Q) / r^3
         const double qx = m[0] * rx + m[1] * ry + m[2] * rz;
         const double qy = m[1] * rx + m[3] * ry + m[4] * rz;
         const double qz = m[2] * rx + m[4] * ry + m[5] * rz;
-        const double rqr = rx * qx + ry * qy + rz * qz;
-        const double tr = m[0] + m[3] + m[5];
-        const double inv5 = inv3 * inv2;
-        const double inv7 = inv5 * inv2;
-        ph += 0.5 * (3.0 * rqr - r2 * tr) * inv5;
-        ex += 7.5 * rqr * rx * inv7 - 3.0 * qx * inv5 - 1.5 * tr * rx * inv5;
-        ey += 7.5 * rqr * ry * inv7 - 3.0 * qy * inv5 - 1.5 * tr * ry * inv5;
-        ez += 7.5 * rqr * rz * inv7 - 3.0 * qz * inv5 - 1.5 * tr * rz * inv5;
+        const double v = (rx * qx + ry * qy + rz * qz) * inv2, tr = m[0] + m[3] + m[5];
+        ph = __builtin_fma(inv3, __builtin_fma(1.5, v, -0.5 * tr), ph);
+        const double inv5 = inv3 * inv2, a = inv5 * __builtin_fma(7.5, v, -1.5 * tr), c = -3.0 * inv5;
+        ex = __builtin_fma(a, rx, __builtin_fma(c, qx, ex));
+        ey = __builtin_fma(a, ry, __builtin_fma(c, qy, ey));
+        ez = __builtin_fma(a, rz, __builtin_fma(c, qz, ez));
     }
 }
-
 
 // Field gradient G_ij = d_i E_j = -d_i d_j phi of the same sources (the
 // second derivatives of the potentials above), accumulated into
@@ -147,18 +158,57 @@ __device__ __forceinline__ void p2p_pair_grad_f32(float rx, float ry, float rz, 
     else pair_grad_terms<S, float>(rx, ry, rz, inv, m0.x, m0.y, m0.z, 0.f, 0.f, 0.f, 0.f, g);
 }
 
-// FP64 near field: physical positions and moments (w values of one order)
+// FP64 near field: physical positions and moments (w values of one order).
+// The same terms as pair_grad_terms with the r_i r_j and mixed terms folded
+// into one vector v, v_i r_j + v_j r_i: two multiply-adds per component.
 template <int S>
 __device__ __forceinline__ void p2p_pair_grad_f64(double rx, double ry, double rz, const double *m, double (&g)[6])
 {
-    const double r2 = rx * rx + ry * ry + rz * rz;
-    double inv = __builtin_amdgcn_rsq(r2);
-    const double hr = 0.5 * r2;
-    inv = inv * __builtin_fma(-hr * inv, inv, 1.5);
-    inv = inv * __builtin_fma(-hr * inv, inv, 1.5);
-    if (S == 2) pair_grad_terms<2, double>(rx, ry, rz, inv, m[0], m[1], m[2], m[3], m[4], m[5], m[0] + m[3] + m[5], g);
-    else if (S == 1) pair_grad_terms<1, double>(rx, ry, rz, inv, m[0], m[1], m[2], 0.0, 0.0, 0.0, 0.0, g);
-    else pair_grad_terms<0, double>(rx, ry, rz, inv, m[0], 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, g);
+    const double inv = rsq_f64(rx * rx + ry * ry + rz * rz);
+    const double inv2 = inv * inv;
+    const double inv3 = inv * inv2;
+    const double r[3] = {rx, ry, rz};
+    double v[3], diag;
+    if constexpr (S == 0) {
+        // q (delta / r^3 - 3 r r / r^5)
+        diag = m[0] * inv3;
+        const double b = -3.0 * diag * inv2;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) v[i] = b * r[i];
+        g[0] += __builtin_fma(v[0], rx, diag);
+        g[1] = __builtin_fma(v[0], ry, g[1]);
+        g[2] = __builtin_fma(v[0], rz, g[2]);
+        g[3] += __builtin_fma(v[1], ry, diag);
+        g[4] = __builtin_fma(v[1], rz, g[4]);
+        g[5] += __builtin_fma(v[2], rz, diag);
+        return;
+    } else if constexpr (S == 1) {
+        // 3 (mu r + r mu + (mu.r) delta) / r^5 - 15 (mu.r) r r / r^7
+        const double mr = m[0] * rx + m[1] * ry + m[2] * rz, a = 3.0 * inv3 * inv2;
+        diag = a * mr;
+        const double b = -2.5 * diag * inv2;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) v[i] = __builtin_fma(a, m[i], b * r[i]);
+    } else {
+        // -3 Q / r^5 + 15 (Qr r + r Qr) / r^7 + diag delta + c r r
+        const double q[3] = {m[0] * rx + m[1] * ry + m[2] * rz, m[1] * rx + m[3] * ry + m[4] * rz,
+                             m[2] * rx + m[4] * ry + m[5] * rz};
+        const double tr = m[0] + m[3] + m[5], inv5 = inv3 * inv2, inv7 = inv5 * inv2;
+        const double w = (rx * q[0] + ry * q[1] + rz * q[2]) * inv2;
+        diag = inv5 * __builtin_fma(7.5, w, -1.5 * tr);
+        const double a = 15.0 * inv7, b = inv7 * __builtin_fma(-26.25, w, 3.75 * tr);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) v[i] = __builtin_fma(a, q[i], b * r[i]);
+        const double c = -3.0 * inv5;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) g[k] = __builtin_fma(c, m[k], g[k]);
+    }
+    g[0] = __builtin_fma(2.0 * v[0], rx, g[0] + diag);
+    g[1] = __builtin_fma(v[0], ry, __builtin_fma(v[1], rx, g[1]));
+    g[2] = __builtin_fma(v[0], rz, __builtin_fma(v[2], rx, g[2]));
+    g[3] = __builtin_fma(2.0 * v[1], ry, g[3] + diag);
+    g[4] = __builtin_fma(v[1], rz, __builtin_fma(v[2], ry, g[4]));
+    g[5] = __builtin_fma(2.0 * v[2], rz, g[5] + diag);
 }
 
 
@@ -256,14 +306,6 @@ __device__ __forceinline__ void p2p_pair_grad_oct_f32(float rx, float ry, float 
 }
 
 // FP64: physical positions and the ten physical components
-__device__ __forceinline__ double rsq_f64(double r2)
-{
-    double inv = __builtin_amdgcn_rsq(r2);
-    const double hr = 0.5 * r2;
-    inv = inv * __builtin_fma(-hr * inv, inv, 1.5);
-    return inv * __builtin_fma(-hr * inv, inv, 1.5);
-}
-
 __device__ __forceinline__ void p2p_pair_oct_f64(double rx, double ry, double rz, const double *m, double &ph,
                                                  double &ex, double &ey, double &ez)
 {
