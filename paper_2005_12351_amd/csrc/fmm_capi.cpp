@@ -427,42 +427,44 @@ hipError_t ctx_pinned(fmm_ctx *ctx, size_t bytes, char **base)
     return hipSuccess;
 }
 
-// Uploads of host vectors into new tree allocations: add() allocates and
-// records the vector's data pointer, flush() packs the data into the
-// context's pinned buffer, queues the copies and records ev_upload after
-// them (the next use of the pinned buffer waits for that event).  Every
-// vector passed to add() must live, unchanged, until flush() returns.
+// Uploads of host vectors into one new tree allocation with one copy: add()
+// records a vector and where its device pointer goes, flush() allocates the
+// block, packs the data into the context's pinned buffer, queues the copy,
+// sets the pointers and records ev_upload after it (the next use of the
+// pinned buffer waits for that event).  A copy costs about as much as a small
+// kernel's launch whatever its size: five vectors in one took 40 us off a
+// build.  Every vector passed to add() must live, unchanged, until flush()
+// returns; *block is the allocation (the pointers lie inside it).
 struct Uploads {
     fmm_tree *t;
     struct Item {
-        void *dst;
+        void **dst;
         const void *src;
         size_t bytes;
     };
     std::vector<Item> items;
     size_t total = 0;
     template <typename T>
-    int add(T **dst, const std::vector<T> &src)
+    void add(T **dst, const std::vector<T> &src)
     {
-        int rc = tree_alloc(t, (void **)dst, src.size() * sizeof(T));
-        if (rc) return rc;
-        if (!src.empty()) {
-            items.push_back(Item{*dst, src.data(), src.size() * sizeof(T)});
-            total += (src.size() * sizeof(T) + 255) / 256 * 256;
-        }
-        return FMM_OK;
+        items.push_back(Item{(void **)dst, src.data(), src.size() * sizeof(T)});
+        total += std::max<size_t>(256, (src.size() * sizeof(T) + 255) / 256 * 256);
     }
-    int flush(hipStream_t s)
+    int flush(hipStream_t s, void **block)
     {
+        *block = nullptr;
         if (items.empty()) return FMM_OK;
+        const int rc = tree_alloc(t, block, total);
+        if (rc) return rc;
         char *base;
         HIPCHK(ctx_pinned(t->ctx, total, &base));
         size_t o = 0;
         for (const Item &it : items) {
-            memcpy(base + o, it.src, it.bytes);
-            HIPCHK(hipMemcpyAsync(it.dst, base + o, it.bytes, hipMemcpyHostToDevice, s));
-            o += (it.bytes + 255) / 256 * 256;
+            if (it.bytes) memcpy(base + o, it.src, it.bytes);
+            *it.dst = (char *)*block + o;
+            o += std::max<size_t>(256, (it.bytes + 255) / 256 * 256);
         }
+        HIPCHK(hipMemcpyAsync(*block, base, total, hipMemcpyHostToDevice, s));
         HIPCHK(hipEventRecord(t->ctx->ev_upload, s));
         t->ctx->upload_pending = true;
         items.clear();
@@ -511,10 +513,9 @@ extern "C" int fmm_build_tree(fmm_ctx *ctx, const double *pos, int64_t n, int nc
     // every tree from 3·10^3 list entries on (builds of 10^3 to 10^4
     // particles: 0.60-1.21 ms against 0.63-2.71 ms)
     dt.tiling = method == FMM_METHOD_FMM && ctx->m2l_schedule != FMM_SCHEDULE_HOST;
-    dt.min_pairs = 0;
     {
         HostScope hs_gpu(ctx, "host:tree_device_build");   // the marked phases plus the release of the build's scratch
-        const hipError_t e = gpu_build_tree(pos, n, ncrit, theta, method == FMM_METHOD_FMM, s, t->ht, ctx, &dt);
+        const hipError_t e = gpu_build_tree(pos, n, ncrit, theta, method == FMM_METHOD_FMM, s, t->ht, ctx, dt);
         if (e != hipSuccess) {
             fmm_tree_destroy(t);
             if (e == hipErrorInvalidValue) FAIL(FMM_EINVAL, "non-finite position");
@@ -545,13 +546,8 @@ extern "C" int fmm_build_tree(fmm_ctx *ctx, const double *pos, int64_t n, int nc
     }
     // leaves, per-particle leaf, non-leaf cells per level, P2P CSR per leaf
     HostScope hs_sched(ctx, "host:tree_near_schedule");
-    std::vector<int32_t> level_cells(nc);
-    for (int64_t c = 0; c < nc; ++c) {
-        level_cells[c] = (int32_t)c;
-        if (h.nchild[c] == 0) {
-            t->leaves.push_back((int32_t)c);
-        }
-    }
+    for (int64_t c = 0; c < nc; ++c)
+        if (h.nchild[c] == 0) t->leaves.push_back((int32_t)c);
     t->nleaves = (int64_t)t->leaves.size();
     const int nlev = (int)h.level_ptr.size() - 1;
     t->level_nonleaf_ptr.assign(nlev + 1, 0);
@@ -702,32 +698,26 @@ extern "C" int fmm_build_tree(fmm_ctx *ctx, const double *pos, int64_t n, int nc
     HostScope hs_up(ctx, "host:tree_upload");
     int rc = FMM_OK;
     Uploads up{t};
-#define UP(dst, vec)                                   \
-    if ((rc = up.add(&(dst), vec)) != FMM_OK) {        \
-        fmm_tree_destroy(t);                           \
-        return rc;                                     \
-    }
-    UP(t->d_leaves, t->leaves);
-    UP(t->d_nonleaf, t->level_nonleaf);
-    UP(t->d_level_cells, level_cells);
-    UP(t->d_p2p_ptr, pptr);
+    up.add(&t->d_leaves, t->leaves);
+    up.add(&t->d_nonleaf, t->level_nonleaf);
+    up.add(&t->d_p2p_ptr, pptr);
     if (dev_src) t->d_p2p_src = dt.p2p_src;
-    else UP(t->d_p2p_src, psrc);
-    UP(t->d_p2p_order, p2p_order);
+    else up.add(&t->d_p2p_src, psrc);
+    up.add(&t->d_p2p_order, p2p_order);
     std::vector<int32_t> cell_slot;   // lives until the flush below
     if (method == FMM_METHOD_FMM && !t->tiling.on_device) {
         const M2LTiling &tl = t->tiling;
-        UP(t->d_ucls, tl.ucls);
-        UP(t->d_usrc, tl.usrc);
+        up.add(&t->d_ucls, tl.ucls);
+        up.add(&t->d_usrc, tl.usrc);
         cell_slot.assign(nc, -1);
         for (size_t k = 0; k < tl.tile_cell.size(); ++k)
             if (tl.tile_cell[k] >= 0) cell_slot[tl.tile_cell[k]] = (int32_t)k;
-        UP(t->d_cell_slot, cell_slot);
-        UP(t->d_cls_geom, tl.cls_geom);
+        up.add(&t->d_cell_slot, cell_slot);
+        up.add(&t->d_cls_geom, tl.cls_geom);
     }
     if (method == FMM_METHOD_FMM) t->work[0] = (double)t->tiling.pairs;
-#undef UP
-    if ((rc = up.flush(s)) || (rc = tree_alloc(t, (void **)&t->d_x, sizeof(double) * 3 * n))) {
+    void *block;   // held until the tree is destroyed
+    if ((rc = up.flush(s, &block)) || (rc = tree_alloc(t, (void **)&t->d_x, sizeof(double) * 3 * n))) {
         fmm_tree_destroy(t);
         return rc;
     }
@@ -771,11 +761,13 @@ static int ensure_expansions(fmm_tree *t, int code, int p, int prec)
     for (void **pp : {(void **)&t->d_mom, (void **)&t->d_mom32, (void **)&t->d_M64, (void **)&t->d_M32, &t->d_Mh,
                       (void **)&t->d_Mf64, (void **)&t->d_part, (void **)&t->d_L64, (void **)&t->d_near, (void **)&t->d_near_g,
                       (void **)&t->d_D64,
-                      (void **)&t->d_D32, (void **)&t->d_sc64, (void **)&t->d_sc32, (void **)&t->d_work,
-                      (void **)&t->d_tile_chunk0, (void **)&t->d_tile_nchunk, (void **)&t->d_wave_ptr}) {
+                      (void **)&t->d_D32, (void **)&t->d_sc64, (void **)&t->d_sc32, &t->d_tables}) {
         tree_free_block(t, *pp);
         *pp = nullptr;
     }
+    // (the work list and the L2P packing lie in d_tables)
+    t->d_work = nullptr;
+    t->d_tile_chunk0 = t->d_tile_nchunk = t->d_wave_ptr = t->d_l2p_pack = nullptr;
     t->dtab_p = -1;
     const int64_t n = t->ht.n, nc = t->ht.ncells();
     const int nm = nterms(p) - nterms(order - 1), nmp = (nm + 3) / 4 * 4, nl = nterms(p - order);
@@ -829,9 +821,10 @@ static int ensure_expansions(fmm_tree *t, int code, int p, int prec)
         for (size_t k = 0; k < work.size(); ++k)
             work[k] = make_int4(t->m2lwork.work[4 * k], t->m2lwork.work[4 * k + 1], t->m2lwork.work[4 * k + 2],
                                 t->m2lwork.work[4 * k + 3]);
-        if ((rc = up.add(&t->d_work, work)) || (rc = up.add(&t->d_tile_chunk0, t->m2lwork.chunk0)) ||
-            (rc = up.add(&t->d_tile_nchunk, t->m2lwork.nchunk)) || (rc = up.add(&t->d_wave_ptr, t->m2lwork.wave_ptr)))
-            return rc;
+        up.add(&t->d_work, work);
+        up.add(&t->d_tile_chunk0, t->m2lwork.chunk0);
+        up.add(&t->d_tile_nchunk, t->m2lwork.nchunk);
+        up.add(&t->d_wave_ptr, t->m2lwork.wave_ptr);
         if ((rc = tree_alloc(t, &t->d_part, es * (size_t)std::max<int64_t>(1, t->m2lwork.nrows) * v.nl_pad)) ||
             (rc = tree_alloc(t, (void **)&t->d_L64, sizeof(double) * nc * (harm ? hterms(p - order) : nl))) ||
             (rc = tree_alloc(t, (void **)&t->d_D64, sizeof(double) * nc_ * v.nd)) ||
@@ -850,7 +843,7 @@ static int ensure_expansions(fmm_tree *t, int code, int p, int prec)
             if ((rc = alloc_state(v.nm_pad))) return rc;
         }
     }
-    if (t->method == FMM_METHOD_FMM && t->l2p_pack_q != p - order) {
+    if (t->method == FMM_METHOD_FMM) {
         // L2P waves: consecutive leaves while they hold at most 64 particles
         // together and fit the layout's budget (a larger leaf gets a wave of
         // its own)
@@ -875,14 +868,10 @@ static int ensure_expansions(fmm_tree *t, int code, int p, int prec)
         std::vector<int32_t> pack_cols = packing(l2p_pack_limit(q, true));
         t->l2p_columns = pack_cols.size() < pack.size() || l2p_columns_pay(q, (int)pack.size() - 1, ncu);
         if (t->l2p_columns) pack.swap(pack_cols);
-        if (t->d_l2p_pack) tree_free_block(t, t->d_l2p_pack);
-        t->d_l2p_pack = nullptr;
-        t->l2p_pack_q = -1;
-        if ((rc = up.add(&t->d_l2p_pack, pack))) return rc;
+        up.add(&t->d_l2p_pack, pack);
         t->l2p_npacks = (int)pack.size() - 1;
-        t->l2p_pack_q = p - order;
     }
-    if ((rc = up.flush(t->ctx->stream))) return rc;
+    if ((rc = up.flush(t->ctx->stream, &t->d_tables))) return rc;
     hipError_t e = t->d_M64 ? launch_fill(t->d_M64, (size_t)(nc + 1) * nmp, t->ctx->stream) : hipSuccess;
     // P2M and M2M write the FP32 copy too; the rest (the zero row the padded
     // M2L slots read, unused levels) stays zero (nmp is a multiple of 4)

@@ -180,7 +180,7 @@ hipError_t dev_sort_pairs(void *tmp, size_t &tmp_bytes, const uint64_t *kin, uin
 
 struct DevKeep;
 hipError_t gpu_build_tree(const double *pos, int64_t n, int ncrit, double theta, bool lists, hipStream_t s,
-                          HostTree &t, fmm_ctx *ctx = nullptr, DevKeep *dt = nullptr);
+                          HostTree &t, fmm_ctx *ctx, DevKeep &dt);
 
 // M2L tiling (tree_host.cpp)
 struct M2LTiling {
@@ -219,7 +219,6 @@ struct DevKeep {
     int32_t *perm = nullptr;
     uint64_t *key = nullptr;
     bool tiling = false;
-    int64_t min_pairs = 0;   // the device tiling only for at least this many M2L pairs
     int32_t *ucls = nullptr, *usrc = nullptr, *cell_slot = nullptr;
     int32_t *m2l_ptr = nullptr, *m2l_src = nullptr;
     // With lists: the P2P sources stay on the device (CSR over the cells by
@@ -330,7 +329,7 @@ struct fmm_tree {
     // device copies
     DevCell *d_cells = nullptr;
     int32_t *d_perm = nullptr, *d_leaves = nullptr;
-    int32_t *d_nonleaf = nullptr, *d_level_cells = nullptr;
+    int32_t *d_nonleaf = nullptr;
     double *d_x = nullptr;                 // sorted positions, SoA x[n] y[n] z[n]
     int32_t *d_p2p_ptr = nullptr, *d_p2p_src = nullptr;   // per leaf, sources as cell ids
     int4 *d_work = nullptr;                // per expansion configuration
@@ -341,7 +340,8 @@ struct fmm_tree {
     int32_t *d_p2p_order = nullptr;        // leaf ordinals by decreasing near-field cost
     int p2p_split = 0;                     // first position of p2p_order past half the near-field cost
     int32_t *d_l2p_pack = nullptr;         // L2P: leaf-ordinal range of every wave
-    int l2p_npacks = 0, l2p_pack_q = -1;
+    int l2p_npacks = 0;
+    void *d_tables = nullptr;              // holds the work list, its chunk tables and the L2P packing
     bool l2p_columns = false;              // L2P keeps the locals as packed columns (see l2p_columns_pay)
     int32_t *d_wave_ptr = nullptr;
     M2LWork m2lwork;

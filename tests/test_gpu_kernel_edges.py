@@ -99,3 +99,61 @@ def test_combine_parts(orc, ctx, n, ncrit, p, s, prec, basis):
     ok &= within(phi.cpu().numpy(), ophi, prec, "phi", floor=PHI_FLOOR)
     t.close()
     assert ok
+
+
+def _tree_equal(gt, o):
+    g = gt.export()
+    assert np.array_equal(g["geom"][:3], o.lo) and g["geom"][3] == o.W
+    for k in ("key", "perm", "level", "ix", "first", "count", "parent", "child0", "nchild", "m2l_ptr", "m2l_src",
+              "p2p_ptr", "p2p_src"):
+        assert g[k].shape == getattr(o, k).shape, k
+        assert np.array_equal(g[k].astype(np.int64), getattr(o, k).astype(np.int64)), k
+
+
+def _points(kind, n):
+    rng = np.random.default_rng(4400 + n)
+    if kind == "cluster":       # one dense cube and a few far particles: long lists, pairs that split the source alone
+        return np.concatenate([0.05 * rng.random((n, 3)), rng.random((40, 3))])
+    if kind == "multi":         # clusters of very different sizes: more pair geometries than are ranked by counting
+        rng = np.random.default_rng(1)
+        return np.concatenate([rng.random(3) + 10.0 ** (-k) * rng.random((n // 6, 3)) for k in (0.5, 1, 1.5, 2, 2.5, 3)])
+    if kind == "same":          # many particles at one place: a chain of cells to the depth cap
+        return np.concatenate([rng.random((n - 20, 3)), np.tile(rng.random((1, 3)), (20, 1))])
+    return rng.random((n, 3))
+
+
+# the tree and the lists against the oracle, whole numbers: workgroups of 256
+# particles (just below, at and above), windows beyond LDS (ncrit > 3840) and
+# beyond the input, one cell, a depth-cap chain, P2P lists beyond the LDS list
+# (1024) and the open pairs beyond theirs
+@pytest.mark.parametrize("kind,n,ncrit,theta", [("uniform", 255, 8, 0.5), ("uniform", 256, 256, 0.5),
+                                                ("uniform", 257, 256, 0.5), ("uniform", 513, 1, 0.6),
+                                                ("uniform", 9000, 4000, 0.5), ("uniform", 9000, 3840, 0.5),
+                                                ("uniform", 9000, 9000, 0.5), ("same", 300, 3, 0.5),
+                                                ("cluster", 4000, 1, 0.3), ("cluster", 4000, 4, 0.7),
+                                                ("multi", 9000, 8, 0.5), ("uniform", 3000, 2, 0.15)])
+def test_tree_and_lists_edges(orc, ctx, kind, n, ncrit, theta):
+    pos = np.ascontiguousarray(_points(kind, n))
+    print(f"[tree edges] {kind} n={n} ncrit={ncrit} theta={theta}", flush=True)
+    gt = fmm.Tree(ctx, torch.from_numpy(pos).cuda(), ncrit, theta)
+    _tree_equal(gt, orc.Tree(pos, ncrit, theta).dump())
+    gt.close()
+
+
+# the device's schedule against the host's where the classes are sorted
+# instead of counted (more than 8192), and just with few of them
+@pytest.mark.parametrize("kind,n,ncrit,theta,many", [("multi", 9000, 1, 0.3, True), ("cluster", 4000, 4, 0.7, False)])
+def test_schedule_class_paths(kind, n, ncrit, theta, many):
+    pos = torch.from_numpy(np.ascontiguousarray(_points(kind, n))).cuda()
+    print(f"[schedule classes] {kind} n={n} ncrit={ncrit} theta={theta}", flush=True)
+    dev, host = fmm.Context(0), fmm.Context(0)
+    host.set_m2l_schedule(fmm.FMM_SCHEDULE_HOST)
+    td, th = fmm.Tree(dev, pos, ncrit, theta), fmm.Tree(host, pos, ncrit, theta)
+    a, b = td.m2l_schedule(), th.m2l_schedule()
+    assert a["where"] == fmm.FMM_SCHEDULE_DEVICE and (td.info()["n_classes"] > 8192) == many
+    for k in ("tile_cell", "tile_uoff", "ucls", "usrc", "cls_geom"):
+        assert a[k].shape == b[k].shape and np.array_equal(a[k], b[k]), k
+    for t in (td, th):
+        t.close()
+    dev.close()
+    host.close()
