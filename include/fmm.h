@@ -250,8 +250,9 @@ enum { FMM_OVERLAP_OFF = 0, FMM_OVERLAP_WHOLE = 1, FMM_OVERLAP_SPLIT = 2, FMM_OV
 int fmm_ctx_set_overlap(fmm_ctx *ctx, int on);
 
 /* Replay HIP graphs (default on): the kernel sequence of fmm_upward and of
- * fmm_evaluate is captured the first time a tree sees a given argument set
- * (moments / output pointers, order, p, precision) and replayed afterwards,
+ * fmm_evaluate is captured the second time a tree sees a given argument set
+ * (moments / output pointers, order, p, precision; the first time it is
+ * launched kernel by kernel) and replayed afterwards,
  * which removes the per-kernel launch cost.  Graphs are never used while
  * profiling is enabled.  Off: kernels are launched one by one. */
 int fmm_ctx_set_graphs(fmm_ctx *ctx, int on);

@@ -381,6 +381,7 @@ struct fmm_tree {
         hipGraphExec_t exec;
     };
     std::vector<GraphEntry> graphs;
+    std::vector<std::vector<int64_t>> seen;   // arguments launched directly so far (captured when they come again)
     double work[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 };
 
