@@ -23,7 +23,49 @@ __global__ void zero_u64_kernel(unsigned long long *p, int n)
     if ((int)threadIdx.x < n) p[threadIdx.x] = 0;
 }
 
+// the sums of the wavefronts that share a group, in their order, to the
+// caller's order; no = 4 (phi, E) or 10 (and the gradient) a particle
+__global__ void bh_reduce_kernel(int n, int split, int no, int outputs, const double *__restrict__ part,
+                                 const int32_t *__restrict__ perm, double *__restrict__ phi,
+                                 double *__restrict__ field, double *__restrict__ grad)
+{
+    const int id = blockIdx.x * blockDim.x + threadIdx.x;
+    if (id >= n * no) return;
+    const int i = id / no, c = id % no;
+    double v = 0.0;
+    for (int k = 0; k < split; ++k) v += part[(size_t)k * n * no + id];
+    const size_t o = (size_t)perm[i];
+    if (c == 0) {
+        if (outputs & FMM_POT) phi[o] = v;
+    } else if (c < 4) {
+        if (outputs & FMM_FIELD) field[3 * o + c - 1] = v;
+    } else if (outputs & FMM_GRAD) {
+        grad[6 * o + c - 4] = v;
+    }
+}
+
 }  // namespace
+
+// Wavefronts a group of 64 particles: as many, up to eight, as keep them within
+// kBHWaves, one a SIMD (what fits of the kernels of the highest orders): they
+// all run side by side then and the launch takes as long as the longest.
+// Passes of 2001 Plummer dipoles, p 6: 569 -> 370 us; 5001 octupoles, FP64:
+// 707 -> 157; 30 011 charges, p 10 (two a group): 1067 -> 627.  With up to 3072
+// wavefronts the orders that fit one a SIMD queue for it and lose (30 011
+// dipoles, p 8, FP64: 1732 -> 2343 us; 1642 with this limit).
+constexpr int kBHWaves = 1024;
+int bh_split(int64_t n)
+{
+    const int64_t groups = (n + 63) / 64;
+    int k = 1;
+    while (k < 8 && 2 * k * groups <= kBHWaves) k *= 2;
+    return k;
+}
+size_t bh_part_doubles(int64_t n)
+{
+    const int k = bh_split(n);
+    return k > 1 ? (size_t)k * n * 10 : 0;
+}
 
 hipError_t launch_bh(fmm_tree *t, int outputs, double *phi, double *field, double *grad, hipStream_t s)
 {
@@ -49,7 +91,14 @@ hipError_t launch_bh(fmm_tree *t, int outputs, double *phi, double *field, doubl
     a.mask = t->smask;
     a.w = mask_width(t->smask);
     a.grad = grad;
+    a.split = bh_split(t->ht.n);
+    a.part = t->d_bhpart;
     hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, s, t->d_bhcount, 2);
-    hipLaunchKernelGGL(k, dim3((unsigned)((t->ht.n + 63) / 64)), dim3(64), 0, s, a);
+    hipLaunchKernelGGL(k, dim3((unsigned)((t->ht.n + 63) / 64) * a.split), dim3(64), 0, s, a);
+    if (a.split > 1) {
+        const int no = (outputs & FMM_GRAD) ? 10 : 4;
+        hipLaunchKernelGGL(bh_reduce_kernel, dim3((unsigned)((t->ht.n * no + 255) / 256)), dim3(256), 0, s, (int)t->ht.n,
+                           a.split, no, outputs, (const double *)t->d_bhpart, t->d_perm, phi, field, grad);
+    }
     return hipGetLastError();
 }

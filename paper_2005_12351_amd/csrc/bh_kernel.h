@@ -11,8 +11,26 @@
 // with an LDS stack of (cell, lane mask); each lane takes its own acceptance
 // decision, in FP64 with the same rounding sequence as the definition above,
 // so every particle accepts exactly the cells it would accept alone and sees
-// them in the same depth-first order.  The cell's multipole and the leaf's
-// sources are identical for all lanes and are read through scalar loads.
+// them in the same depth-first order.  The leaf's sources are identical for
+// all lanes and are read through scalar loads.
+//
+// What bounds it is the vector issue of the M2P evaluation (about 600
+// operations at p 6), which half the lanes sat out: neighbours accept the same
+// regions at different cells, one the parent, the other its children.  So in
+// the harmonic basis an accepted cell's row is copied to one of kSlots places
+// in LDS and each accepting lane only marks the place; when the places run out
+// every lane evaluates the lowest place it has marked, in rounds, as long as
+// most lanes take part.  A lane then still evaluates its own cells with the
+// same operations; its sums add up in another order (FP64).  From p 6 on
+// (10^6 Plummer dipoles, theta 0.6, p 6, MIXED: 3.75 -> 3.50 ms; 30 011 charges,
+// p 10: 1.41 -> 1.07 ms; below, the places cost more than they save: p 4, 100k
+// quadrupoles 0.76 -> 0.79 ms) and in the harmonic basis; otherwise each cell is
+// evaluated as it is accepted, its row through scalar loads.
+//
+// A small system fills few wavefronts and then waits for the longest: `split`
+// of them share a group of particles.  All walk the cells above level
+// kOwnLevel; of those and of that level's each takes the cells (and all below
+// them) whose index has its residue.  bh_reduce_kernel adds their sums in order.
 #pragma once
 #include <cmath>
 
@@ -39,6 +57,8 @@ struct BHArgs {
     unsigned long long *counts;   // [0] accepted (particle, cell) pairs, [1] direct pairs
     int mask, w;                  // source orders present (bit mask), FP64 moments per particle
     double *grad;                 // field gradient (n x 6), kernels with GRAD only
+    int split;                    // wavefronts that share a group of 64 particles (1, 2, 4 or 8)
+    double *part;                 // their sums, split x n x (4 or, with GRAD, 10)
 };
 
 constexpr int kStack = 8 * (kMaxLevel + 3);
@@ -52,6 +72,18 @@ __device__ __forceinline__ void wave_sync_bh()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// row places of a wave, and the lanes below which a round waits for more marks
+constexpr int kSlots = 32;
+constexpr int kRoundLanes = 36;
+constexpr int kOwnLevel = 3;
+
+// 16 bytes a lane from global memory to LDS, the lanes' data back to back
+__device__ __forceinline__ void copy_row(const void *g, void *lds)
+{
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)g,
+                                     (__attribute__((address_space(3))) void *)lds, 16, 0, 0);
+}
+
 // H: the rows are folded onto the harmonic basis and contracted by M2PEvalH
 // GRAD: also the field gradient, G_ij = -(1/r^3) sum M~ D_{n+e_i+e_j}(u) for
 // an accepted cell and the pairs' closed forms for a leaf
@@ -59,11 +91,13 @@ template <int P, int S, typename T, bool H, bool GRAD>
 __global__ __launch_bounds__(64) void bh_kernel(BHArgs a)
 {
     constexpr bool F32 = sizeof(T) == 4;
+    constexpr bool PLACES = H && P >= 6;
     constexpr int W = (S + 1) * (S + 2) / 2;
     __shared__ int stk_c[kStack];
     __shared__ unsigned long long stk_m[kStack];
     const int lane = threadIdx.x;
-    const int i = blockIdx.x * 64 + lane;
+    const int share = blockIdx.x & (a.split - 1), group = blockIdx.x / a.split;
+    const int i = group * 64 + lane;
     const bool valid = i < a.n;
     const int ii = valid ? i : a.n - 1;
     const size_t n = a.n;
@@ -80,6 +114,63 @@ __global__ __launch_bounds__(64) void bh_kernel(BHArgs a)
     wave_sync_bh();
     const T *Mb = (const T *)a.M;
     unsigned int n_m2p = 0, n_p2p = 0;
+    // M2P of one cell in the normalised form: u = (x - z)/r,
+    // phi = (1/r) sum M~ D(u), E = -(1/r^2) sum M~ D_{+e}(u)
+    auto m2p = [&](const T *Mc, double dx, double dy, double dz, double r) {
+        const double ir = 1.0 / r;
+        T p_, x_, y_, z_;
+        const T ux = (T)(dx * ir), uy = (T)(dy * ir), uz = (T)(dz * ir);
+        if constexpr (GRAD) {
+            T gg[6];
+            if constexpr (H) M2PEvalGH<P, S, T>::eval(Mc, ux, uy, uz, p_, x_, y_, z_, gg);
+            else M2PEvalG<P, S, T>::eval(Mc, ux, uy, uz, p_, x_, y_, z_, gg);
+            const double ir3 = ir * ir * ir;
+#pragma unroll
+            for (int q = 0; q < 6; ++q) g[q] -= (double)gg[q] * ir3;
+        } else if constexpr (H) {
+            M2PEvalH<P, S, T>::eval(Mc, ux, uy, uz, p_, x_, y_, z_);
+        } else {
+            M2PEval<P, S, T>::eval(Mc, ux, uy, uz, p_, x_, y_, z_);
+        }
+        ph += (double)p_ * ir;
+        const double ir2 = ir * ir;
+        ex -= (double)x_ * ir2;
+        ey -= (double)y_ * ir2;
+        ez -= (double)z_ * ir2;
+    };
+    // places: rows of 16-byte units, an odd number of them apart so that
+    // lanes at different places read different banks
+    constexpr int kRow16 = (int)((hterms(P) - hterms(S - 1)) * sizeof(T) + 15) / 16;
+    constexpr int kStride = (kRow16 | 1) * 16 / (int)sizeof(T);
+    static_assert(kRow16 <= 64, "one copy a row");
+    __shared__ alignas(16) T rows[PLACES ? kSlots : 1][PLACES ? kStride : 4];
+    __shared__ alignas(16) double geo[PLACES ? kSlots : 1][4];   // centre, half side
+    unsigned used = 0;       // places taken (the same for the wave)
+    unsigned pend = 0;       // places this lane has marked
+    // rounds of evaluations; all: until no lane has a mark, else while most
+    // lanes do or no place is free
+    auto rounds = [&](bool all) {
+        __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): the rows are in LDS
+        wave_sync_bh();
+        for (;;) {
+            const unsigned long long m = __ballot(pend != 0);
+            if (m == 0) break;
+            if (!all && __popcll(m) < kRoundLanes) {
+                unsigned u = pend;
+                for (int o = 1; o < 64; o <<= 1) u |= __shfl_xor(u, o, 64);
+                if (u != 0xffffffffu) break;
+            }
+            if (pend) {
+                const int s = __builtin_ctz(pend);
+                pend &= pend - 1;
+                m2p(rows[s], __dsub_rn(xi, geo[s][0]), __dsub_rn(yi, geo[s][1]), __dsub_rn(zi, geo[s][2]), geo[s][3]);
+            }
+        }
+        used = pend;
+        for (int o = 1; o < 64; o <<= 1) used |= __shfl_xor(used, o, 64);
+        used = __builtin_amdgcn_readfirstlane(used);
+        wave_sync_bh();
+    };
     while (sp > 0) {
         --sp;
         const int c = stk_c[sp];
@@ -98,35 +189,31 @@ __global__ __launch_bounds__(64) void bh_kernel(BHArgs a)
         const bool accept = mine && !inside && (__dmul_rn(r, r) < __dmul_rn(a.theta2, d2));
         const unsigned long long acc_m = __ballot(accept);
         const unsigned long long rest = mask & ~acc_m;
-        if (accept) {
-            ++n_m2p;
-            // M2P in the normalised form: u = (x - z)/r, phi = (1/r) sum M~ D(u),
-            // E = -(1/r^2) sum M~ D_{+e}(u)
-            const double ir = 1.0 / r;
-            T p_, x_, y_, z_;
-            const T *Mc = Mb + (size_t)c * a.nmp;
-            const T ux = (T)(dx * ir), uy = (T)(dy * ir), uz = (T)(dz * ir);
-            if constexpr (GRAD) {
-                T gg[6];
-                if constexpr (H) M2PEvalGH<P, S, T>::eval(Mc, ux, uy, uz, p_, x_, y_, z_, gg);
-                else M2PEvalG<P, S, T>::eval(Mc, ux, uy, uz, p_, x_, y_, z_, gg);
-                const double ir3 = ir * ir * ir;
-#pragma unroll
-                for (int q = 0; q < 6; ++q) g[q] -= (double)gg[q] * ir3;
-            } else if constexpr (H) {
-                M2PEvalH<P, S, T>::eval(Mc, ux, uy, uz, p_, x_, y_, z_);
-            } else {
-                M2PEval<P, S, T>::eval(Mc, ux, uy, uz, p_, x_, y_, z_);
+        const bool own = cell.level >= kOwnLevel || (c & (a.split - 1)) == share;
+        if constexpr (PLACES) {
+            if (acc_m && own) {
+                if (used == 0xffffffffu) rounds(false);
+                const int s = __builtin_ctz(~used);
+                used |= 1u << s;
+                if (lane < kRow16) copy_row((const char *)(Mb + (size_t)c * a.nmp) + 16 * lane, rows[s]);
+                if (lane == 0) {
+                    geo[s][0] = zx;
+                    geo[s][1] = zy;
+                    geo[s][2] = zz;
+                    geo[s][3] = r;
+                }
+                if (accept) {
+                    ++n_m2p;
+                    pend |= 1u << s;
+                }
             }
-            ph += (double)p_ * ir;
-            const double ir2 = ir * ir;
-            ex -= (double)x_ * ir2;
-            ey -= (double)y_ * ir2;
-            ez -= (double)z_ * ir2;
+        } else if (accept && own) {
+            ++n_m2p;
+            m2p(Mb + (size_t)c * a.nmp, dx, dy, dz, r);
         }
         if (rest) {
             if (cell.nchild == 0) {
-                if ((rest >> lane) & 1ull) {
+                if (own && ((rest >> lane) & 1ull)) {
                     n_p2p += (unsigned)cell.count - (inside ? 1u : 0u);
                     if (a.mask != (1 << S)) {
                         // several source orders: each order's closed form, FP64
@@ -204,17 +291,22 @@ __global__ __launch_bounds__(64) void bh_kernel(BHArgs a)
                     }
                 }
             } else {
-                // children in reverse, so that they are visited in octant order
-                if (lane == 0)
-                    for (int k = cell.nchild - 1; k >= 0; --k) {
-                        stk_c[sp + (cell.nchild - 1 - k)] = cell.child0 + k;
-                        stk_m[sp + (cell.nchild - 1 - k)] = rest;
-                    }
-                sp += cell.nchild;
+                // children in reverse, so that they are visited in octant
+                // order, a lane each; of those at kOwnLevel this wavefront's
+                const bool keep = lane < cell.nchild && (cell.level != kOwnLevel - 1 ||
+                                                         ((cell.child0 + lane) & (a.split - 1)) == share);
+                const unsigned long long km = __ballot(keep);
+                if (keep) {
+                    const int at = sp + __popcll(km >> lane) - 1;   // those after it lie below
+                    stk_c[at] = cell.child0 + lane;
+                    stk_m[at] = rest;
+                }
+                sp += __popcll(km);
                 wave_sync_bh();
             }
         }
     }
+    if constexpr (PLACES) rounds(true);
     // interaction counts of the wave, one atomic per wave
     unsigned long long c0 = n_m2p, c1 = n_p2p;
     for (int o = 32; o > 0; o >>= 1) {
@@ -224,6 +316,18 @@ __global__ __launch_bounds__(64) void bh_kernel(BHArgs a)
     if (lane == 0) {
         atomicAdd(&a.counts[0], c0);
         atomicAdd(&a.counts[1], c1);
+    }
+    if (valid && a.split > 1) {
+        constexpr int NO = GRAD ? 10 : 4;
+        double *o = a.part + ((size_t)share * n + i) * NO;
+        o[0] = ph;
+        o[1] = ex;
+        o[2] = ey;
+        o[3] = ez;
+        if constexpr (GRAD)
+#pragma unroll
+            for (int q = 0; q < 6; ++q) o[4 + q] = g[q];
+        return;
     }
     if (valid) {
         const size_t o = (size_t)a.perm[i];

@@ -810,6 +810,10 @@ static int ensure_expansions(fmm_tree *t, int code, int p, int prec)
     if (t->method == FMM_METHOD_BH && !t->d_bhcount &&
         (rc = tree_alloc(t, (void **)&t->d_bhcount, 2 * sizeof(unsigned long long))))
         return rc;
+    // (here, not in the evaluation, which allocates nothing)
+    if (t->method == FMM_METHOD_BH && !t->d_bhpart && bh_part_doubles(n) &&
+        (rc = tree_alloc(t, (void **)&t->d_bhpart, sizeof(double) * bh_part_doubles(n))))
+        return rc;
     if (!fmm && harm) {
         // folded rows the Barnes-Hut M2P reads (FMM trees size them from the M2L variant below)
         const size_t es = prec == FMM_PREC_MIXED ? sizeof(float) : sizeof(double);

@@ -347,6 +347,7 @@ struct fmm_tree {
     M2LWork m2lwork;
     double *d_cls_geom = nullptr;
     unsigned long long *d_bhcount = nullptr;   // Barnes-Hut interaction counters (2)
+    double *d_bhpart = nullptr;            // sums of wavefronts that share a group (bh_part_doubles)
     // per expansion state
     int have_up = 0, order = 0, p = 0, prec = 0, dtab_p = -1;   // order: the lowest source order s
     int smask = 1;                         // source orders present (bit mask)
@@ -438,6 +439,8 @@ constexpr int64_t kNoAllocMaxN = 1 << 18;
 hipError_t noalloc_scratch(int device, double **ptr);
 int l2p_pack_limit(int q, bool cols);   // leaves one L2P wave may take at expansion order q, per layout
 bool l2p_columns_pay(int q, int npacks, int ncu);   // L2P layout choice for a launch of npacks waves
+// doubles of the tree's d_bhpart for n particles (0: none used)
+size_t bh_part_doubles(int64_t n);
 hipError_t launch_bh(fmm_tree *t, int outputs, double *phi, double *field, double *grad, hipStream_t s);
 // P2P over the leaves p2p_order[first .. first + count) (count < 0: to the end)
 hipError_t launch_p2p_part(fmm_tree *t, hipStream_t s, int first, int count);

@@ -157,3 +157,29 @@ def test_schedule_class_paths(kind, n, ncrit, theta, many):
         t.close()
     dev.close()
     host.close()
+
+
+# Barnes-Hut: one wavefront a group, two and eight; rows through places in LDS
+# (p >= 6) and not; a root that is a leaf, a tree that ends above and below the
+# level whose cells are shared out, a last group of one particle
+@pytest.mark.parametrize("n,ncrit,p,s,kind", [(1, 8, 6, 0, "uniform"), (40, 64, 6, 1, "uniform"), (65, 8, 6, 1, "uniform"),
+                                              (129, 4, 5, 2, "plummer"), (2000, 64, 7, 1, "uniform"),
+                                              (3000, 2, 6, 3, "plummer"), (9000, 16, 6, 0, "plummer"),
+                                              (20001, 32, 6, 1, "uniform"), (40000, 64, 4, 1, "plummer")])
+@pytest.mark.parametrize("prec", [FP64, MIXED])
+def test_barnes_hut_shares(orc, ctx, n, ncrit, p, s, kind, prec):
+    w = _workload(4500 + n, s, n, kind, p, ncrit)
+    print(f"[bh shares] n={n} ncrit={ncrit} p={p} s={s} {kind} precision={prec}", flush=True)
+    t = fmm.Tree(ctx, to_dev(w.pos), ncrit, 0.5, fmm.FMM_METHOD_BH)
+    t.upward(s, to_dev(w.moments), p, prec)
+    phi, E = t.evaluate()
+    _, _, G = t.evaluate_grad()
+    torch.cuda.synchronize()
+    tg = np.arange(n) if n <= 3000 else np.sort(np.random.default_rng(3).choice(n, 1500, replace=False))
+    ophi, oE, oG = orc.Tree(w.pos, ncrit).bh(w.order, w.moments, p, 0.5, targets=tg, want_grad=True)
+    ok = within(E.cpu().numpy()[tg], oE, prec, "E")
+    ok &= within(phi.cpu().numpy()[tg], ophi, prec, "phi", floor=PHI_FLOOR)
+    # the gradient's bounds: as in the gradient parity test
+    ok &= within(G.cpu().numpy()[tg], oG, prec, "G", None if prec == FP64 else (2e-6, 1e-4))
+    t.close()
+    assert ok
