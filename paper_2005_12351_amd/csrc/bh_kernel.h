@@ -22,7 +22,7 @@
 // every lane evaluates the lowest place it has marked, in rounds, as long as
 // most lanes take part.  A lane then still evaluates its own cells with the
 // same operations; its sums add up in another order (FP64).  From p 6 on
-// (10^6 Plummer dipoles, theta 0.6, p 6, MIXED: 3.75 -> 3.50 ms; 30 011 charges,
+// (10^6 Plummer dipoles, theta 0.6, p 6, MIXED: 3.75 -> 3.55 ms; 30 011 charges,
 // p 10: 1.41 -> 1.07 ms; below, the places cost more than they save: p 4, 100k
 // quadrupoles 0.76 -> 0.79 ms) and in the harmonic basis; otherwise each cell is
 // evaluated as it is accepted, its row through scalar loads.
