@@ -1,6 +1,7 @@
 """Builds libfmm.so for gfx950 in-tree (paper_2005_12351_amd/libfmm.so).
 
-Steps: generate the unrolled M2L kernels (csrc/gen_m2l.py) into _build/gen,
+Steps: generate the unrolled M2L kernels (csrc/gen_m2l.py), the Barnes-Hut
+terms (csrc/gen_bh.py) and the shift tables (csrc/gen_shift.py) into _build/gen,
 compile every translation unit with hipcc (in parallel), link the shared
 library.  Host-only tree code is compiled without floating-point contraction
 so that the quantisation and acceptance tests round as specified.
@@ -30,8 +31,10 @@ def _sources(gen_dir, gen_opt):
     sys.path.insert(0, CSRC)
     import gen_bh  # noqa: E402
     import gen_m2l  # noqa: E402
+    import gen_shift  # noqa: E402
     gen = gen_m2l.main(gen_dir, gen_opt)
     gen_bh_tus = gen_bh.main(gen_dir)
+    gen_shift.main(gen_dir)
     sys.path.pop(0)
     srcs = [(os.path.join(CSRC, "p2p_lo.hip"), []),
             (os.path.join(CSRC, "p2p_oct.hip"), []),

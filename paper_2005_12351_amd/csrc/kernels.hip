@@ -621,129 +621,86 @@ hipError_t launch_p2m(fmm_tree *t, hipStream_t s)
 }
 
 // ------------------------------------------------------------------ M2M / L2L
-// Both shifts act per child octant sigma (child centre = parent centre +
-// sigma r_child) and factorise over the axes, so each is applied as three 1-D
-// passes over a coefficient row held in LDS.  One workgroup per parent cell:
-// threadIdx.y = child slot (up to 8), threadIdx.x = coefficient slot; every
-// thread keeps the multi-indices of its coefficients and its child's octant
-// signs in registers, so the passes touch LDS only.
-constexpr int kShiftX = 128;                     // coefficient slots per child
-constexpr int kShiftItems = (nterms(kPTable) + kShiftX - 1) / kShiftX;
+// Both shifts are fixed sparse matrices whose entries change sign from octant to
+// octant only by the parities x of n - m: a character of the octant, (-1)^(x.c)
+// (gen_shift.py, which writes the matrices).  So a parent's children share one
+// product: M2M takes for every class x the children's rows summed under its
+// character, L2L sums every class once and combines the eight sums for each
+// child.  Eight lanes work on one component, lane x on class x; before (M2M) or
+// after (L2L) the product the same lanes stand for the octants, and the change
+// between the two is an eight-point Walsh-Hadamard transform over them.
+//
+// A level takes as long as its chain of loads (parent, children, rows) when it
+// has few parents, and its table reads when it has many.  2608 products a
+// parent at p 10 in the harmonic basis (8008 with every component), against
+// three passes along the axes of every child's whole row with an index
+// computed for each term before.  All levels together, M2M and L2L: p 10 dipoles,
+// 4096 leaves of an even tree 51 and 38 -> 24 and 21 us; 10^6 Plummer
+// dipoles, p 6, nine levels 150 and 144 -> 79 and 75; 2 x 10^6 quadrupoles, p 10, 320 and
+// 171 -> 80 and 62.
+constexpr int kShiftThreads = 256;
+#include "shift_tables.h"
+static_assert(kShiftOrders == FMM_P_MAX, "the shift tables end at another order");
 
-struct ShiftItems {
-    int n;                                       // items owned by this thread
-    int m[kShiftItems][3];
-    int k[kShiftItems];
-};
-
-__device__ __forceinline__ void shift_items(int nt, ShiftItems &it)
+__device__ __forceinline__ double octant_transform(double v, int lane)
 {
-    it.n = 0;
 #pragma unroll
-    for (int j = 0; j < kShiftItems; ++j) {
-        const int i = threadIdx.x + j * kShiftX;
-        const MultiIndex nn = k_mi.v[i < nt ? i : 0];
-        it.m[j][0] = nn.x;
-        it.m[j][1] = nn.y;
-        it.m[j][2] = nn.z;
-        it.k[j] = nn.k;
-        if (i < nt) it.n = j + 1;
+    for (int m = 1; m < 8; m <<= 1) {
+        const double o = __shfl_xor(v, m);
+        v = (lane & m) ? o - v : v + o;
+    }
+    return v;
+}
+
+// sum of val[e] src[idx[e] - first] over the entries [b, e)
+__device__ __forceinline__ double shift_row(const uint16_t *__restrict__ idx, const double *__restrict__ val, int b,
+                                            int e, const double *src, int first)
+{
+    double acc = 0.0;
+#pragma unroll 4
+    for (int i = b; i < e; ++i) acc = fma(val[i], src[idx[i] - first], acc);
+    return acc;
+}
+
+// children of `P` by octant: slot[c] = the child's cell, -1 where there is none
+__device__ __forceinline__ void shift_children(const DevCell *__restrict__ cells, int P, int *slot)
+{
+    const int tid = threadIdx.x;
+    if (tid < 8) slot[tid] = -1;   // one wavefront writes both, in order
+    const int nch = cells[P].nchild, kid0 = cells[P].child0;
+    __builtin_amdgcn_wave_barrier();
+    if (tid < nch) {
+        const DevCell cc = cells[kid0 + tid];
+        slot[(cc.ix & 1) << 2 | (cc.iy & 1) << 1 | (cc.iz & 1)] = kid0 + tid;
     }
 }
 
-// M~_n(P) = sum_children 2^-|n| sum_{k <= n} prod_d (-sigma_d)^k_d / k_d! M~_{n-k}(C)
-// (Eq. 4 read with new-minus-old centre; radii halve from child to parent).
-// Children are summed in octant order in FP64.  Harmonic basis (M null): the
-// children's folded rows Mh64, lifted with zeros at m_z >= 2, are shifted
-// and the parent's row is folded again (the fold commutes with the shift:
-// what it drops is r^2 times a lower row, which the shift keeps so).
-// (8 waves per SIMD: two 1024-thread workgroups fit a CU)
-__global__ __launch_bounds__(kShiftX * 8, 8) void m2m_kernel(int p, int s, int nmp, const int32_t *__restrict__ parents,
-                                                          const DevCell *__restrict__ cells, double *__restrict__ M,
-                                                          float *__restrict__ M32, int nhp, float *__restrict__ Mh32,
-                                                          double *__restrict__ Mh64)
+// rows of n components from the order s on, `stride` apart; Ms: FP32 copy or null
+template <bool HARM>
+__global__ __launch_bounds__(kShiftThreads) void m2m_kernel(int s, int n, int stride,
+                                                            const int32_t *__restrict__ parents,
+                                                            const DevCell *__restrict__ cells, double *__restrict__ M,
+                                                            float *__restrict__ Ms)
 {
-    extern __shared__ double sm[];   // X[8][nt], Y[8][nt]
-    const int nt = nterms(p), n0 = nterms(s - 1);
-    double *X = sm, *Y = sm + 8 * nt;
-    __shared__ double inv_fact[kPTable + 2];
-    const int P = parents[blockIdx.x];
-    const int nch = cells[P].nchild, kid0 = cells[P].child0;
-    const int k = threadIdx.y;
-    const int tid = threadIdx.y * kShiftX + threadIdx.x;
-    if (tid <= kPTable + 1) {
-        double f = 1.0;
-        for (int a = 1; a <= tid; ++a) f *= k_inv.v[a];
-        inv_fact[tid] = f;
-    }
-    ShiftItems it;
-    shift_items(nt, it);
-    double sg[3] = {1.0, 1.0, 1.0};   // -sigma_d
-    if (k < nch) {
-        const DevCell cc = cells[kid0 + k];
-        sg[0] = (cc.ix & 1) ? -1.0 : 1.0;
-        sg[1] = (cc.iy & 1) ? -1.0 : 1.0;
-        sg[2] = (cc.iz & 1) ? -1.0 : 1.0;
-#pragma unroll
-        for (int j = 0; j < kShiftItems; ++j) {
-            if (j >= it.n) break;
-            const int i = threadIdx.x + j * kShiftX;
-            double v = 0.0;
-            if (i >= n0) {
-                if (M) v = M[(size_t)(kid0 + k) * nmp + (i - n0)];
-                else if (it.m[j][2] <= 1)
-                    v = Mh64[(size_t)(kid0 + k) * nhp + hindex(it.m[j][0], it.m[j][1], it.m[j][2]) - hterms(s - 1)];
-            }
-            X[k * nt + i] = v;
-        }
-    }
+    extern __shared__ double W[];   // [8][n]
+    __shared__ int slot[8];
+    const int P = parents[blockIdx.x], x = threadIdx.x & 7;
+    const int first = HARM ? hterms(s - 1) : nterms(s - 1);
+    shift_children(cells, P, slot);
     __syncthreads();
-    // pass d: dst_n = sum_{a <= n_d} (-sigma_d)^a / a! src_{n - a e_d}
+    const int kid = slot[x];
+    // eight lanes of a component leave a loop together
+    for (int h = threadIdx.x >> 3; h < n; h += kShiftThreads / 8)
+        W[x * n + h] = octant_transform(kid >= 0 ? M[(size_t)kid * stride + h] : 0.0, x);
+    __syncthreads();
+    for (int h = threadIdx.x >> 3; h < n; h += kShiftThreads / 8) {
+        const uint16_t *off = HARM ? kM2MH_off[(h + first) * 8 + x] : kM2MF_off[(h + first) * 8 + x];
+        double v = shift_row(HARM ? kM2MH_idx : kM2MF_idx, HARM ? kM2MH_val : kM2MF_val, off[s], off[kShiftOrders + 1],
+                             W + x * n, first);
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const double *src = (d == 1 ? Y : X) + k * nt;
-        double *dst = (d == 1 ? X : Y) + k * nt;
-        if (k < nch) {
-#pragma unroll
-            for (int j = 0; j < kShiftItems; ++j) {
-                if (j >= it.n) break;
-                int mx = it.m[j][0], my = it.m[j][1], mz = it.m[j][2];
-                const int nd = d == 0 ? mx : (d == 1 ? my : mz);
-                double acc = 0.0, sp = 1.0;
-                for (int a = 0; a <= nd; ++a) {
-                    acc = fma(sp * inv_fact[a], src[mindex(mx, my, mz)], acc);
-                    mx -= d == 0;
-                    my -= d == 1;
-                    mz -= d == 2;
-                    sp *= sg[d];
-                }
-                dst[threadIdx.x + j * kShiftX] = acc;
-            }
-        }
-        __syncthreads();
-    }
-    if (k == 0)
-#pragma unroll
-        for (int j = 0; j < kShiftItems; ++j) {
-            if (j >= it.n) break;
-            const int i = threadIdx.x + j * kShiftX;
-            if (i < n0) continue;
-            double acc = 0.0;
-            for (int c = 0; c < nch; ++c) acc += Y[c * nt + i];
-            const double v = ldexp(acc, -it.k[j]);
-            if (M) M[(size_t)P * nmp + (i - n0)] = v;
-            if (M32) M32[(size_t)P * nmp + (i - n0)] = (float)v;
-            X[i] = v;   // X is free after the last pass
-        }
-    if (Mh32 || Mh64) {
-        // the harmonic-basis rows: the FP64 state and the M2L's copy
-        __syncthreads();
-        const int h0 = hterms(s - 1), nh = hterms(p) - h0;
-        for (int h = tid; h < nh; h += kShiftX * 8) {
-            const double v = fold_component(X, h + h0);
-            if (Mh32) Mh32[(size_t)P * nhp + h] = (float)v;
-            if (Mh64) Mh64[(size_t)P * nhp + h] = v;
-        }
+        for (int m = 1; m < 8; m <<= 1) v += __shfl_xor(v, m);
+        if (x == 0) M[(size_t)P * stride + h] = v;
+        if (x == 1 && Ms) Ms[(size_t)P * stride + h] = (float)v;
     }
 }
 
@@ -751,11 +708,17 @@ hipError_t launch_m2m_level(fmm_tree *t, int level, hipStream_t s)
 {
     const int a = t->level_nonleaf_ptr[level], b = t->level_nonleaf_ptr[level + 1];
     if (b <= a) return hipSuccess;
-    const int nmp = (nterms(t->p) - nterms(t->order - 1) + 3) / 4 * 4;
-    const size_t lds = (size_t)16 * nterms(t->p) * sizeof(double);
     const HarmOut ho = harm_out(t);
-    hipLaunchKernelGGL(m2m_kernel, dim3(b - a), dim3(kShiftX, 8), lds, s, t->p, t->order, nmp, t->d_nonleaf + a,
-                       t->d_cells, t->d_M64, t->prec == FMM_PREC_MIXED ? t->d_M32 : nullptr, ho.nhp, ho.h32, ho.h64);
+    if (ho.h64) {
+        const int n = hterms(t->p) - hterms(t->order - 1);
+        hipLaunchKernelGGL(m2m_kernel<true>, dim3(b - a), dim3(kShiftThreads), 8 * n * sizeof(double), s, t->order, n,
+                           ho.nhp, t->d_nonleaf + a, t->d_cells, ho.h64, ho.h32);
+    } else {
+        const int n = nterms(t->p) - nterms(t->order - 1);
+        hipLaunchKernelGGL(m2m_kernel<false>, dim3(b - a), dim3(kShiftThreads), 8 * n * sizeof(double), s, t->order, n,
+                           (n + 3) / 4 * 4, t->d_nonleaf + a, t->d_cells, t->d_M64,
+                           t->prec == FMM_PREC_MIXED ? t->d_M32 : nullptr);
+    }
     return hipGetLastError();
 }
 
@@ -778,105 +741,24 @@ constexpr RebuildTable make_rebuild()
 }
 __constant__ RebuildTable k_rebuild = make_rebuild();
 
-// rebuilt component (a, b, 2j + r) of a harmonic local row from its n_z <= 1
-// components R (stride 1, harmonic order): (-1)^j sum_i C(j, i)
-// R[(a + 2i, b + 2(j - i), r)]
-__device__ __forceinline__ double rebuild_local(const double *R, int a, int b, int c)
+// locals: rows of n components, up to the order q
+template <bool HARM>
+__global__ __launch_bounds__(kShiftThreads) void l2l_kernel(int q, int n, const int32_t *__restrict__ parents,
+                                                            const DevCell *__restrict__ cells, double *__restrict__ L)
 {
-    const int j = c >> 1, r = c & 1;
-    double acc = 0.0;
-    for (int i = 0; i <= j; ++i) acc = fma(k_rebuild.w[j][i], R[hindex(a + 2 * i, b + 2 * (j - i), r)], acc);
-    return acc;
-}
-
-// L~_n(C) += sum_{a: |n+a| <= q} prod_d sigma_d^a_d / a_d! * 2^-(|n+a|+1) L~_{n+a}(P)
-// (Taylor shift of the local expansion to the child centre, in the
-// normalised form).  The parent row is scaled once and shared by the
-// children of the workgroup.  Harmonic basis (nlh > 0): rows hold the n_z
-// <= 1 components; the parent's row is rebuilt in LDS and only the
-// children's n_z <= 1 components are updated (the shift keeps the row
-// harmonic, so the others follow from them).
-__global__ __launch_bounds__(kShiftX * 8, 8) void l2l_kernel(int q, int nlh, const int32_t *__restrict__ parents,
-                                                          const DevCell *__restrict__ cells, double *__restrict__ L)
-{
-    extern __shared__ double sm[];   // Pr[nl], X[8][nl], Y[8][nl], R[nlh]
-    const int nl = nterms(q);
-    double *Pr = sm, *X = sm + nl, *Y = sm + 9 * nl, *R = sm + 17 * nl;
-    __shared__ double inv_fact[kPTable + 2];
-    const int P = parents[blockIdx.x];
-    const int nch = cells[P].nchild, kid0 = cells[P].child0;
-    const int k = threadIdx.y;
-    const int tid = threadIdx.y * kShiftX + threadIdx.x;
-    if (tid <= kPTable + 1) {
-        double f = 1.0;
-        for (int a = 1; a <= tid; ++a) f *= k_inv.v[a];
-        inv_fact[tid] = f;
-    }
-    ShiftItems it;
-    shift_items(nl, it);
-    if (nlh > 0) {
-        for (int h = tid; h < nlh; h += kShiftX * 8) R[h] = L[(size_t)P * nlh + h];
-        __syncthreads();
-    }
-    if (nlh > 0) {
-        // the parent's row rebuilt by the whole workgroup
-        for (int i = tid; i < nl; i += kShiftX * 8) {
-            const MultiIndex nn = k_mi.v[i];
-            Pr[i] = ldexp(rebuild_local(R, nn.x, nn.y, nn.z), -(nn.k + 1));
-        }
-    } else if (k == 0) {
-#pragma unroll
-        for (int j = 0; j < kShiftItems; ++j) {
-            if (j >= it.n) break;
-            const int i = threadIdx.x + j * kShiftX;
-            Pr[i] = ldexp(L[(size_t)P * nl + i], -(it.k[j] + 1));
-        }
-    }
-    double sg[3] = {1.0, 1.0, 1.0};   // sigma_d
-    if (k < nch) {
-        const DevCell cc = cells[kid0 + k];
-        sg[0] = (cc.ix & 1) ? 1.0 : -1.0;
-        sg[1] = (cc.iy & 1) ? 1.0 : -1.0;
-        sg[2] = (cc.iz & 1) ? 1.0 : -1.0;
-    }
+    extern __shared__ double row[];   // [n], the parent's
+    __shared__ int slot[8];
+    const int P = parents[blockIdx.x], x = threadIdx.x & 7;
+    shift_children(cells, P, slot);
+    for (int h = threadIdx.x; h < n; h += kShiftThreads) row[h] = L[(size_t)P * n + h];
     __syncthreads();
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const double *src = d == 0 ? Pr : (d == 1 ? Y : X) + k * nl;
-        double *dst = (d == 1 ? X : Y) + k * nl;
-        if (k < nch) {
-#pragma unroll
-            for (int j = 0; j < kShiftItems; ++j) {
-                if (j >= it.n) break;
-                int mx = it.m[j][0], my = it.m[j][1], mz = it.m[j][2];
-                double acc = 0.0, sp = 1.0;
-                for (int a = 0; a <= q - it.k[j]; ++a) {
-                    acc = fma(sp * inv_fact[a], src[mindex(mx, my, mz)], acc);
-                    mx += d == 0;
-                    my += d == 1;
-                    mz += d == 2;
-                    sp *= sg[d];
-                }
-                dst[threadIdx.x + j * kShiftX] = acc;
-            }
-        }
-        __syncthreads();
-    }
-    if (k < nch) {
-        if (nlh > 0) {
-            for (int h = threadIdx.x; h < nlh; h += kShiftX) {
-                int a, b, c;
-                hmulti(h, a, b, c);
-                L[(size_t)(kid0 + k) * nlh + h] += Y[k * nl + mindex(a, b, c)];
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < kShiftItems; ++j) {
-                if (j >= it.n) break;
-                const int i = threadIdx.x + j * kShiftX;
-                L[(size_t)(kid0 + k) * nl + i] += Y[k * nl + i];
-            }
-        }
+    const int kid = slot[x];
+    for (int h = threadIdx.x >> 3; h < n; h += kShiftThreads / 8) {
+        const double old = kid >= 0 ? L[(size_t)kid * n + h] : 0.0;
+        const uint16_t *off = HARM ? kL2LH_off[h * 8 + x] : kL2LF_off[h * 8 + x];
+        const double v = octant_transform(
+            shift_row(HARM ? kL2LH_idx : kL2LF_idx, HARM ? kL2LH_val : kL2LF_val, off[0], off[q + 1], row, 0), x);
+        if (kid >= 0) L[(size_t)kid * n + h] = old + v;
     }
 }
 
@@ -886,10 +768,10 @@ hipError_t launch_l2l_level(fmm_tree *t, int level, hipStream_t s)
     const int a = t->level_nonleaf_ptr[level - 1], b = t->level_nonleaf_ptr[level];
     if (b <= a) return hipSuccess;
     const int q = t->p - t->order;
-    const int nlh = t->basis == FMM_M2L_HARMONIC ? hterms(q) : 0;
-    const size_t lds = (size_t)(17 * nterms(q) + nlh) * sizeof(double);
-    hipLaunchKernelGGL(l2l_kernel, dim3(b - a), dim3(kShiftX, 8), lds, s, q, nlh, t->d_nonleaf + a, t->d_cells,
-                       t->d_L64);
+    const bool harm = t->basis == FMM_M2L_HARMONIC;
+    const int n = harm ? hterms(q) : nterms(q);
+    hipLaunchKernelGGL(harm ? l2l_kernel<true> : l2l_kernel<false>, dim3(b - a), dim3(kShiftThreads),
+                       n * sizeof(double), s, q, n, t->d_nonleaf + a, t->d_cells, t->d_L64);
     return hipGetLastError();
 }
 

@@ -183,3 +183,28 @@ def test_barnes_hut_shares(orc, ctx, n, ncrit, p, s, kind, prec):
     ok &= within(G.cpu().numpy()[tg], oG, prec, "G", None if prec == FP64 else (2e-6, 1e-4))
     t.close()
     assert ok
+
+
+# the shifts' row cuts (lowest and highest p and s), parents of one to eight
+# children, chains of single children, both bases
+@pytest.mark.parametrize("basis", [fmm.FMM_M2L_HARMONIC, fmm.FMM_M2L_FULL])
+@pytest.mark.parametrize("p,s,n,ncrit,kind", [(1, 0, 90, 1, "plummer"), (2, 1, 200, 2, "uniform"), (4, 3, 300, 4, "plummer"),
+                                              (10, 0, 500, 8, "plummer"), (10, 3, 400, 8, "uniform")])
+def test_shift_edges(orc, ctx, basis, p, s, n, ncrit, kind):
+    w = _workload(4700 + n, s, n, kind, p, ncrit)
+    print(f"[shift] p={p} s={s} n={n} ncrit={ncrit} {kind} basis={basis}", flush=True)
+    ctx.set_m2l_basis(basis)
+    try:
+        ok = True
+        for prec in (FP64, MIXED):
+            t = fmm.Tree(ctx, to_dev(w.pos), ncrit, w.theta)
+            t.upward(w.order, to_dev(w.moments), p, prec)
+            phi, E = t.evaluate()
+            torch.cuda.synchronize()
+            rphi, rE = orc.Tree(w.pos, ncrit, w.theta).fmm(w.order, w.moments, p)[:2]
+            ok &= within(phi.cpu().numpy(), rphi, prec, "phi", floor=PHI_FLOOR)
+            ok &= within(E.cpu().numpy(), rE, prec, "field")
+            t.close()
+    finally:
+        ctx.set_m2l_basis(fmm.FMM_M2L_HARMONIC)
+    assert ok
