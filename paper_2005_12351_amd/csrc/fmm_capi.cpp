@@ -864,7 +864,7 @@ static int ensure_expansions(fmm_tree *t, int code, int p, int prec)
     }
     if (t->method == FMM_METHOD_FMM) {
         // L2P waves: consecutive leaves while they hold at most 64 particles
-        // together and fit the layout's budget (a larger leaf gets a wave of
+        // together and no more than the kernel takes (a larger leaf gets a wave of
         // its own)
         auto packing = [&](int kmax) {
             std::vector<int32_t> pk(1, 0);
@@ -882,11 +882,15 @@ static int ensure_expansions(fmm_tree *t, int code, int p, int prec)
             return pk;
         };
         const int q = p - order;
-        pack = packing(l2p_pack_limit(q, false));
-        const int ncu = t->ctx->ncu;
-        std::vector<int32_t> pack_cols = packing(l2p_pack_limit(q, true));
-        t->l2p_columns = pack_cols.size() < pack.size() || l2p_columns_pay(q, (int)pack.size() - 1, ncu);
-        if (t->l2p_columns) pack.swap(pack_cols);
+        if (harm) {
+            pack = packing(l2p_harmonic_leaves());
+        } else {
+            pack = packing(l2p_pack_limit(q, false));
+            std::vector<int32_t> pack_cols = packing(l2p_pack_limit(q, true));
+            t->l2p_columns =
+                pack_cols.size() < pack.size() || l2p_columns_pay(q, (int)pack.size() - 1, t->ctx->ncu);
+            if (t->l2p_columns) pack.swap(pack_cols);
+        }
         up.add(&t->d_l2p_pack, pack);
         t->l2p_npacks = (int)pack.size() - 1;
     }

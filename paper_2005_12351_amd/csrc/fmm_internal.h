@@ -437,7 +437,8 @@ hipError_t launch_l2p_final(fmm_tree *t, int outputs, double *phi, double *field
 // current device, resolved once per device
 constexpr int64_t kNoAllocMaxN = 1 << 18;
 hipError_t noalloc_scratch(int device, double **ptr);
-int l2p_pack_limit(int q, bool cols);   // leaves one L2P wave may take at expansion order q, per layout
+int l2p_harmonic_leaves();              // leaves one L2P wave may take in the harmonic basis
+int l2p_pack_limit(int q, bool cols);   // the same in the full basis at expansion order q, per layout
 bool l2p_columns_pay(int q, int npacks, int ncu);   // L2P layout choice for a launch of npacks waves
 // doubles of the tree's d_bhpart for n particles (0: none used)
 size_t bh_part_doubles(int64_t n);

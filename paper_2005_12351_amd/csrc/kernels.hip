@@ -722,25 +722,6 @@ hipError_t launch_m2m_level(fmm_tree *t, int level, hipStream_t s)
     return hipGetLastError();
 }
 
-// (-1)^j C(j, i) for j <= FMM_P_MAX / 2: the weights that rebuild a
-// harmonic row's component (a, b, 2j + r) from those with n_z <= 1
-struct RebuildTable {
-    double w[FMM_P_MAX / 2 + 1][FMM_P_MAX / 2 + 1];
-};
-constexpr RebuildTable make_rebuild()
-{
-    RebuildTable t{};
-    for (int j = 0; j <= FMM_P_MAX / 2; ++j) {
-        double c = 1.0;
-        for (int i = 0; i <= j; ++i) {
-            t.w[j][i] = (j & 1) ? -c : c;
-            c = c * (j - i) / (i + 1);
-        }
-    }
-    return t;
-}
-__constant__ RebuildTable k_rebuild = make_rebuild();
-
 // locals: rows of n components, up to the order q
 template <bool HARM>
 __global__ __launch_bounds__(kShiftThreads) void l2l_kernel(int q, int n, const int32_t *__restrict__ parents,
@@ -863,6 +844,7 @@ static hipError_t launch_p2p_range(fmm_tree *t, hipStream_t s, bool grad, int fi
 // the cube's LDS share limits the resident waves (1M particles and more,
 // where they are about 25 % faster); the cube otherwise.  The leaves per pack
 // are what a 16 KB budget of the layout allows.
+// This is the kernel of the full basis (harmonic rows: l2p_harmonic_kernel).
 // Compiled per q = p - s.
 constexpr int kL2PMaxLeaves = 8;
 constexpr int kL2PPackBudget = 16384;   // bytes of (q+2)^3 cubes that fix the leaves per pack
@@ -880,6 +862,7 @@ int l2p_pack_limit(int q, bool cols)
 {
     return std::max(1, std::min(kL2PMaxLeaves, kL2PPackBudget / (8 * (cols ? l2p_cols(q) : l2p_cube(q)))));
 }
+int l2p_harmonic_leaves() { return kL2PMaxLeaves; }
 constexpr int kLdsPerCU = 160 * 1024;
 bool l2p_columns_pay(int q, int npacks, int ncu)
 {
@@ -895,8 +878,7 @@ template <int Q, bool GRAD, bool COLS>
 __global__ __launch_bounds__(64) void l2p_kernel(int outputs, const int32_t *__restrict__ pack,
                                                  const int32_t *__restrict__ leaves, const DevCell *__restrict__ cells,
                                                  Geo g, const double *__restrict__ xs, int n,
-                                                 const double *__restrict__ L, int nlh,
-                                                 const double *__restrict__ near, const int32_t *__restrict__ perm,
+                                                 const double *__restrict__ L, const double *__restrict__ near, const int32_t *__restrict__ perm,
                                                  double *__restrict__ phi, double *__restrict__ field,
                                                  const double *__restrict__ near_g, double *__restrict__ grad)
 {
@@ -928,33 +910,9 @@ __global__ __launch_bounds__(64) void l2p_kernel(int outputs, const int32_t *__r
     }
     for (int q = 0; q < nlv; ++q) {
         const size_t c = (size_t)leaves[p0 + q];
-        if (nlh > 0) {
-            // harmonic basis: the n_z <= 1 components, the rest below
-            for (int h = threadIdx.x; h < nlh; h += blockDim.x) {
-                int a, b, z;
-                hmulti(h, a, b, z);
-                cubes[q * NC + at(a, b) + z] = L[c * nlh + h];
-            }
-        } else {
-            for (int i = threadIdx.x; i < NL; i += blockDim.x) {
-                const MultiIndex nn = k_mi.v[i];
-                cubes[q * NC + at(nn.x, nn.y) + nn.z] = L[c * NL + i];
-            }
-        }
-    }
-    if (nlh > 0) {
-        // (a, b, 2j + r) = (-1)^j sum_i C(j, i) (a + 2i, b + 2(j - i), r):
-        // reads only n_z <= 1 entries, writes only n_z >= 2 ones
-        __syncthreads();
-        for (int it = threadIdx.x; it < nlv * NL; it += blockDim.x) {
-            const int q = it / NL;
-            const MultiIndex nn = k_mi.v[it % NL];
-            if (nn.z < 2) continue;
-            double *cube = cubes + q * NC;
-            const int j = nn.z >> 1, r = nn.z & 1;
-            double acc = 0.0;
-            for (int i = 0; i <= j; ++i) acc = fma(k_rebuild.w[j][i], cube[at(nn.x + 2 * i, nn.y + 2 * (j - i)) + r], acc);
-            cube[at(nn.x, nn.y) + nn.z] = acc;
+        for (int i = threadIdx.x; i < NL; i += blockDim.x) {
+            const MultiIndex nn = k_mi.v[i];
+            cubes[q * NC + at(nn.x, nn.y) + nn.z] = L[c * NL + i];
         }
     }
     __syncthreads();
@@ -1038,23 +996,172 @@ __global__ __launch_bounds__(64) void l2p_kernel(int outputs, const int32_t *__r
     }
 }
 
+// Harmonic basis.  With F_h, h = (a, b, r), the fold of the row eta^n/n!, the
+// expansion is sum_h L~_h F_h, and the fold commutes with derivatives:
+//   d_x F(a,b,r) = F(a-1,b,r),  d_y F(a,b,r) = F(a,b-1,r),
+//   d_z F(a,b,1) = F(a,b,0),    d_z F(a,b,0) = -F(a-2,b,1) - F(a,b-2,1),
+// so the gradient of order l is entries of order l - 1, and Euler's identity
+// l F = eta . grad F gives order l itself, as it gives the potential of each
+// order from its field.  One pass over the row then reads every coefficient once
+// and has nothing to rebuild; the second derivatives come from order l - 2, and
+// zz = -xx - yy.  The sums over monomials read each coefficient four times from
+// LDS, which bound them: 2 x 10^6 targets, q 8: 475 -> 102 us; 10^6, q 5: 74 -> 33;
+// 100k, q 9: 59 -> 14.  With the gradient, 400k targets: q 4 48 -> 30 us, q 8 200 ->
+// 71, q 10 332 -> 148 (there the orders no longer fit the registers).  What bounds
+// it now: the FP64 operations at high q, the targets' own traffic at low q.
+__host__ __device__ constexpr int horder(int a, int b, int r) { return b + r == 0 ? 0 : 2 * (b + r) - 1 + r; }
+
+// component (a, b, r) of the order held in F, zero where an index is negative
+__device__ __forceinline__ double hat(const double *F, int a, int b, int r)
+{
+    return a < 0 || b < 0 ? 0.0 : F[horder(a, b, r)];
+}
+
+// d_z of component (a, b, r), from the entries F of one order less, and whether
+// it has any term
+__host__ __device__ constexpr bool hat_dz_any(int a, int b, int r)
+{
+    return a >= 0 && b >= 0 && (r || a >= 2 || b >= 2);
+}
+__device__ __forceinline__ double hat_dz(const double *F, int a, int b, int r)
+{
+    if (a < 0 || b < 0) return 0.0;
+    if (r) return F[horder(a, b, 0)];
+    if (a < 2) return -hat(F, a, b - 2, 1);
+    if (b < 2) return -hat(F, a - 2, b, 1);
+    return -(hat(F, a - 2, b, 1) + hat(F, a, b - 2, 1));
+}
+
+struct L2PSums {
+    double ph, fx, fy, fz, gxx, gxy, gxz, gyy, gyz;
+};
+
+// orders l.. of the row: F1, F2 hold the orders l - 1 and l - 2 (one array an
+// order, so that all stay in registers)
+template <int Q, bool GRAD, int l>
+__device__ __forceinline__ void l2p_orders(const double *row, const double *F1, const double *F2, double ex, double ey,
+                                           double ez, L2PSums &o)
+{
+    if constexpr (l <= Q) {
+        const double hx = ex * (1.0 / l), hy = ey * (1.0 / l), hz = ez * (1.0 / l);
+        double sx = 0.0, sy = 0.0, sz = 0.0;
+        double F0[2 * l + 1];
+#pragma unroll
+        for (int j = 0; j <= 2 * l; ++j) {
+            const int t = (j + 1) / 2, r = j == 0 ? 0 : j - (2 * t - 1), a = l - t, b = t - r;
+            const double c = row[l * l + j];
+            const double dx = hat(F1, a - 1, b, r), dy = hat(F1, a, b - 1, r), dz = hat_dz(F1, a, b, r);
+            // terms that are zero by their indices are left out
+            const bool zx = a >= 1, zy = b >= 1, zz = hat_dz_any(a, b, r);
+            if (l < Q) {
+                double v = 0.0;
+                if (zx) v = hx * dx;
+                if (zy) v = fma(hy, dy, v);
+                if (zz) v = fma(hz, dz, v);
+                F0[j] = v;
+            }
+            if (zx) sx = fma(c, dx, sx);
+            if (zy) sy = fma(c, dy, sy);
+            if (zz) sz = fma(c, dz, sz);
+            if constexpr (GRAD && l >= 2) {
+                if (a >= 2) o.gxx = fma(c, hat(F2, a - 2, b, r), o.gxx);
+                if (zx && zy) o.gxy = fma(c, hat(F2, a - 1, b - 1, r), o.gxy);
+                if (b >= 2) o.gyy = fma(c, hat(F2, a, b - 2, r), o.gyy);
+                if (hat_dz_any(a - 1, b, r)) o.gxz = fma(c, hat_dz(F2, a - 1, b, r), o.gxz);
+                if (hat_dz_any(a, b - 1, r)) o.gyz = fma(c, hat_dz(F2, a, b - 1, r), o.gyz);
+            }
+        }
+        o.fx += sx;
+        o.fy += sy;
+        o.fz += sz;
+        o.ph = fma(hx, sx, fma(hy, sy, fma(hz, sz, o.ph)));
+        l2p_orders<Q, GRAD, l + 1>(row, F0, F1, ex, ey, ez, o);
+    }
+}
+
+template <int Q, bool GRAD>
+__global__ __launch_bounds__(64) void l2p_harmonic_kernel(int outputs, const int32_t *__restrict__ pack,
+                                                          const int32_t *__restrict__ leaves,
+                                                          const DevCell *__restrict__ cells, Geo g,
+                                                          const double *__restrict__ xs, int n,
+                                                          const double *__restrict__ L, const double *__restrict__ near,
+                                                          const int32_t *__restrict__ perm, double *__restrict__ phi,
+                                                          double *__restrict__ field, const double *__restrict__ near_g,
+                                                          double *__restrict__ grad)
+{
+    constexpr int NH = hterms(Q);
+    __shared__ double rows[kL2PMaxLeaves * NH];
+    __shared__ int lfirst[kL2PMaxLeaves], lstart[kL2PMaxLeaves + 1];
+    __shared__ double lgeo[kL2PMaxLeaves][4];    // centre, 1 / radius
+    const int p0 = pack[blockIdx.x], nlv = pack[blockIdx.x + 1] - p0;
+    if ((int)threadIdx.x < nlv) {
+        const DevCell c = cells[leaves[p0 + threadIdx.x]];
+        double z[3];
+        cell_center(c, g.lo, g.h, z);
+        lfirst[threadIdx.x] = c.first;
+        lstart[threadIdx.x + 1] = c.count;
+        lgeo[threadIdx.x][0] = z[0];
+        lgeo[threadIdx.x][1] = z[1];
+        lgeo[threadIdx.x][2] = z[2];
+        lgeo[threadIdx.x][3] = 1.0 / cell_radius(c.level, g.h);
+    }
+    for (int q = 0; q < nlv; ++q) {
+        const size_t c = (size_t)leaves[p0 + q];
+        for (int h = threadIdx.x; h < NH; h += 64) rows[q * NH + h] = L[c * NH + h];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        lstart[0] = 0;
+        for (int q = 0; q < nlv; ++q) lstart[q + 1] += lstart[q];
+    }
+    __syncthreads();
+    const int tot = lstart[nlv];
+    for (int k = threadIdx.x; k < tot; k += 64) {
+        int q = 0;
+        while (q + 1 < nlv && k >= lstart[q + 1]) ++q;
+        const int i = lfirst[q] + (k - lstart[q]);
+        const double *row = rows + q * NH;
+        const double ir = lgeo[q][3];
+        const double ex = (xs[i] - lgeo[q][0]) * ir, ey = (xs[n + i] - lgeo[q][1]) * ir,
+                     ez = (xs[2 * (size_t)n + i] - lgeo[q][2]) * ir;
+        L2PSums v{row[0], 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        const double one[1] = {1.0};
+        l2p_orders<Q, GRAD, 1>(row, one, one, ex, ey, ez, v);
+        const double *nr = near + 4 * (size_t)i;
+        const size_t o = (size_t)perm[i];
+        if (outputs & FMM_POT) phi[o] = v.ph * ir + nr[0];
+        if (outputs & FMM_FIELD) {
+            const double ir2 = ir * ir;
+            field[3 * o] = -v.fx * ir2 + nr[1];
+            field[3 * o + 1] = -v.fy * ir2 + nr[2];
+            field[3 * o + 2] = -v.fz * ir2 + nr[3];
+        }
+        if constexpr (GRAD) {
+            const double ir3 = ir * ir * ir;
+            const double *ng = near_g + 6 * (size_t)i;
+            const double G[6] = {v.gxx, v.gxy, v.gxz, v.gyy, v.gyz, -(v.gxx + v.gyy)};
+#pragma unroll
+            for (int c = 0; c < 6; ++c) grad[6 * o + c] = -G[c] * ir3 + ng[c];
+        }
+    }
+}
+
 template <int Q, bool COLS>
 static void l2p_launch_layout(fmm_tree *t, int outputs, double *phi, double *field, double *grad, hipStream_t s,
                               const double *near_g)
 {
     Geo g{{t->ht.lo[0], t->ht.lo[1], t->ht.lo[2]}, t->ht.h};
     const size_t lds = (size_t)l2p_pack_limit(Q, COLS) * (COLS ? l2p_cols(Q) : l2p_cube(Q)) * sizeof(double);
-    const int nlh = t->basis == FMM_M2L_HARMONIC ? hterms(Q) : 0;
     if constexpr (Q >= 2) {
         if (outputs & FMM_GRAD) {
             hipLaunchKernelGGL((l2p_kernel<Q, true, COLS>), dim3((unsigned)t->l2p_npacks), dim3(64), lds, s, outputs,
-                               t->d_l2p_pack, t->d_leaves, t->d_cells, g, t->d_x, (int)t->ht.n, t->d_L64, nlh,
+                               t->d_l2p_pack, t->d_leaves, t->d_cells, g, t->d_x, (int)t->ht.n, t->d_L64,
                                t->d_near, t->d_perm, phi, field, near_g, grad);
             return;
         }
     }
     hipLaunchKernelGGL((l2p_kernel<Q, false, COLS>), dim3((unsigned)t->l2p_npacks), dim3(64), lds, s, outputs,
-                       t->d_l2p_pack, t->d_leaves, t->d_cells, g, t->d_x, (int)t->ht.n, t->d_L64, nlh, t->d_near,
+                       t->d_l2p_pack, t->d_leaves, t->d_cells, g, t->d_x, (int)t->ht.n, t->d_L64, t->d_near,
                        t->d_perm, phi, field, nullptr, nullptr);
 }
 
@@ -1062,7 +1169,15 @@ template <int Q>
 static void l2p_launch(fmm_tree *t, int outputs, double *phi, double *field, double *grad, hipStream_t s,
                        const double *near_g)
 {
-    if (t->l2p_columns) l2p_launch_layout<Q, true>(t, outputs, phi, field, grad, s, near_g);
+    if (t->basis == FMM_M2L_HARMONIC) {
+        Geo g{{t->ht.lo[0], t->ht.lo[1], t->ht.lo[2]}, t->ht.h};
+        auto kernel = l2p_harmonic_kernel<Q, false>;
+        if constexpr (Q >= 2)
+            if (outputs & FMM_GRAD) kernel = l2p_harmonic_kernel<Q, true>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)t->l2p_npacks), dim3(64), 0, s, outputs, t->d_l2p_pack, t->d_leaves,
+                           t->d_cells, g, t->d_x, (int)t->ht.n, t->d_L64, t->d_near, t->d_perm, phi, field, near_g,
+                           grad);
+    } else if (t->l2p_columns) l2p_launch_layout<Q, true>(t, outputs, phi, field, grad, s, near_g);
     else l2p_launch_layout<Q, false>(t, outputs, phi, field, grad, s, near_g);
 }
 

@@ -208,3 +208,29 @@ def test_shift_edges(orc, ctx, basis, p, s, n, ncrit, kind):
     finally:
         ctx.set_m2l_basis(fmm.FMM_M2L_HARMONIC)
     assert ok
+
+
+# L2P of harmonic rows at the orders where its unrolled length changes most
+# (one, two, the longest), packs of as many leaves as a wavefront takes, leaves
+# of more than 64 targets
+@pytest.mark.parametrize("p,s,n,ncrit,kind", [(2, 1, 60, 4, "uniform"), (1, 0, 300, 4, "plummer"), (3, 1, 500, 2, "uniform"),
+                                              (9, 2, 700, 200, "uniform"), (10, 1, 900, 130, "plummer"),
+                                              (10, 0, 400, 3, "uniform")])
+def test_l2p_edges(orc, ctx, p, s, n, ncrit, kind):
+    w = _workload(4800 + n, s, n, kind, p, ncrit)
+    print(f"[l2p] p={p} s={s} n={n} ncrit={ncrit} {kind}", flush=True)
+    t = fmm.Tree(ctx, to_dev(w.pos), ncrit, w.theta)
+    t.upward(s, to_dev(w.moments), p, FP64)
+    grad = p - s >= 2
+    if grad:
+        phi, E, G = t.evaluate_grad()
+    else:
+        phi, E = t.evaluate()
+    torch.cuda.synchronize()
+    o = orc.Tree(w.pos, ncrit, w.theta).fmm(w.order, w.moments, p, want_grad=grad)
+    ok = within(phi.cpu().numpy(), o[0], FP64, "phi", floor=PHI_FLOOR)
+    ok &= within(E.cpu().numpy(), o[1], FP64, "E")
+    if grad:
+        ok &= within(G.cpu().numpy(), o[2], FP64, "G")
+    t.close()
+    assert ok
