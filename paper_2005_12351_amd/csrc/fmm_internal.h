@@ -73,39 +73,7 @@ __host__ __device__ inline void hmulti(int h, int &nx, int &ny, int &nz)
 //   sum_j (-1)^j sum_i C(j,i) row[(a - 2i, b - 2(j - i), r + 2j)],
 // which carries the row's contraction with any harmonic tensor D (such as
 // the derivatives of 1/r, D_{k+2e_x} + D_{k+2e_y} + D_{k+2e_z} = 0) onto the
-// components with m_z <= 1 without changing it; the order is kept.  The
-// terms are tabulated once: for h, entries [start[h], start[h+1]) hold the
-// row index and the signed binomial weight.
-constexpr int kFoldTerms = 1036;   // terms of all components up to order kPTable
-struct FoldTable {
-    int16_t start[hterms(kPTable) + 1];
-    int16_t idx[kFoldTerms];
-    float w[kFoldTerms];
-};
-constexpr FoldTable make_fold()
-{
-    FoldTable f{};
-    int e = 0, h = 0;
-    for (int l = 0; l <= kPTable; ++l)
-        for (int t = 0; t <= l; ++t)
-            for (int r = 0; r <= (t == 0 ? 0 : 1); ++r) {
-                f.start[h++] = (int16_t)e;
-                const int a = l - t, b = t - r;
-                for (int j = 0; 2 * j <= a + b; ++j) {
-                    int c = 1;   // C(j, i)
-                    for (int i = 0; i <= j; ++i) {
-                        if (a - 2 * i >= 0 && b - 2 * (j - i) >= 0) {
-                            f.idx[e] = (int16_t)mindex(a - 2 * i, b - 2 * (j - i), r + 2 * j);
-                            f.w[e] = (float)((j & 1) ? -c : c);
-                            ++e;
-                        }
-                        c = c * (j - i) / (i + 1);
-                    }
-                }
-            }
-    f.start[h] = (int16_t)e;
-    return f;
-}
+// components with m_z <= 1 without changing it; the order is kept.
 
 // multi-indices in storage order (total order ascending; within an order
 // n_x descending, then n_y descending), up to order kPTable

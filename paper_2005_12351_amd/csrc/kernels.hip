@@ -141,7 +141,8 @@ __device__ __forceinline__ void sort_moments(size_t i, int mask, const double *_
 // k over the source orders present (MASK bit k), so a system with several
 // orders adds each part's expansion.  One workgroup per leaf; particles are
 // staged in LDS 32 at a time as per-axis tables X_a = zeta_x^a/a! (and Y, Z).
-// Two kernels, chosen by the source orders:
+// Harmonic rows have a kernel of their own (p2m_harmonic_kernel).  Full basis:
+// two kernels, chosen by the source orders:
 // - p2m_coef_kernel (charges and dipoles, and any system with octupoles): a
 //   thread owns one or more coefficients n and adds every particle's term,
 //   1 + 3 (+ 6 + 10) products of table entries per particle;
@@ -176,18 +177,6 @@ constexpr InvTable make_inv()
 }
 __constant__ InvTable k_inv = make_inv();   // 1/a
 
-static __constant__ FoldTable k_fold = make_fold();
-static_assert(make_fold().start[hterms(kPTable)] == kFoldTerms, "fold table size");
-
-// component h of the harmonic-basis fold of a multipole row (row indexed by
-// multi-index)
-__device__ __forceinline__ double fold_component(const double *row, int h)
-{
-    double acc = 0.0;
-    for (int e = k_fold.start[h]; e < k_fold.start[h + 1]; ++e) acc = fma((double)k_fold.w[e], row[k_fold.idx[e]], acc);
-    return acc;
-}
-
 template <int MASK>
 __global__ __launch_bounds__(kP2MThreads) void p2m_coef_kernel(int p, int nmp, const int32_t *__restrict__ leaves,
                                                           const DevCell *__restrict__ cells, Geo g,
@@ -195,8 +184,7 @@ __global__ __launch_bounds__(kP2MThreads) void p2m_coef_kernel(int p, int nmp, c
                                                           const double *__restrict__ mom_user,
                                                           const int32_t *__restrict__ perm, double *__restrict__ mom64,
                                                           float *__restrict__ mom32, double *__restrict__ M,
-                                                          float *__restrict__ M32, int nhp, float *__restrict__ Mh32,
-                                                          double *__restrict__ Mh64)
+                                                          float *__restrict__ M32)
 {
     constexpr int W = mask_width(MASK);
     constexpr int S = mask_min_order(MASK);
@@ -320,25 +308,13 @@ __global__ __launch_bounds__(kP2MThreads) void p2m_coef_kernel(int p, int nmp, c
             acc[k] = a;
         }
     }
-    __shared__ double row[nterms(FMM_P_MAX)];   // the finished row, indexed by multi-index
 #pragma unroll
     for (int k = 0; k < KMAX; ++k)
         if ((int)threadIdx.x + k * kP2MThreads < nm) {
             const size_t o = (size_t)c * nmp + threadIdx.x + k * kP2MThreads;
-            if (M) M[o] = acc[k];              // full basis: the FP64 upward state
-            if (M32) M32[o] = (float)acc[k];   // the copy the full-basis mixed-precision M2L reads
-            row[n0 + threadIdx.x + k * kP2MThreads] = acc[k];
+            M[o] = acc[k];                     // the FP64 upward state
+            if (M32) M32[o] = (float)acc[k];   // the copy the mixed-precision M2L reads
         }
-    if (Mh32 || Mh64) {
-        // the harmonic-basis row the M2L reads (in its precision)
-        __syncthreads();
-        const int h0 = hterms(S - 1), nh = hterms(p) - h0;
-        for (int h = threadIdx.x; h < nh; h += kP2MThreads) {
-            const double v = fold_component(row, h + h0);
-            if (Mh32) Mh32[(size_t)c * nhp + h] = (float)v;
-            if (Mh64) Mh64[(size_t)c * nhp + h] = v;
-        }
-    }
 }
 
 // Column blocks of every (p, s), fixed at compile time: for each pair the
@@ -412,8 +388,7 @@ __global__ __launch_bounds__(kP2MThreads) void p2m_kernel(int p, int nmp, int bl
                                                           const double *__restrict__ mom_user,
                                                           const int32_t *__restrict__ perm, double *__restrict__ mom64,
                                                           float *__restrict__ mom32, double *__restrict__ M,
-                                                          float *__restrict__ M32, int nhp, float *__restrict__ Mh32,
-                                                          double *__restrict__ Mh64)
+                                                          float *__restrict__ M32)
 {
     constexpr int W = mask_width(MASK);
     constexpr int S = mask_min_order(MASK);
@@ -422,7 +397,6 @@ __global__ __launch_bounds__(kP2MThreads) void p2m_kernel(int p, int nmp, int bl
     __shared__ double pw[kP2MStage][3][kAxW];
     __shared__ double sv[kP2MStage][10];
     __shared__ double gsum[kP2MThreads * kP2MBlk];   // sums of groups 1.. (ngroups > 1)
-    __shared__ double row[nterms(FMM_P_MAX)];          // the finished row, indexed by multi-index
     const int c = leaves[blockIdx.x];
     const DevCell cell = cells[c];
     double z[3];
@@ -537,20 +511,9 @@ __global__ __launch_bounds__(kP2MThreads) void p2m_kernel(int p, int nmp, int bl
             if (k >= nb) break;
             const int i = mindex(ax, ay, az0 + k);
             const size_t o = (size_t)c * nmp + (i - n0);
-            if (M) M[o] = acc[k];              // full basis: the FP64 upward state
-            if (M32) M32[o] = (float)acc[k];   // the copy the full-basis mixed-precision M2L reads
-            row[i] = acc[k];
+            M[o] = acc[k];                     // the FP64 upward state
+            if (M32) M32[o] = (float)acc[k];   // the copy the mixed-precision M2L reads
         }
-    if (Mh32 || Mh64) {
-        // the harmonic-basis row the M2L reads (in its precision)
-        __syncthreads();
-        const int h0 = hterms(S - 1), nh = hterms(p) - h0;
-        for (int h = threadIdx.x; h < nh; h += kP2MThreads) {
-            const double v = fold_component(row, h + h0);
-            if (Mh32) Mh32[(size_t)c * nhp + h] = (float)v;
-            if (Mh64) Mh64[(size_t)c * nhp + h] = v;
-        }
-    }
 }
 
 // harmonic-basis rows written by P2M and M2M (null when unused): the FP64
@@ -575,6 +538,184 @@ static HarmOut harm_out(const fmm_tree *t)
     return o;
 }
 
+// Functions of a harmonic row: F_h(eta), h = (a, b, r) with r <= 1, the fold of
+// eta^n / n!.  The fold commutes with derivatives,
+//   d_x F(a,b,r) = F(a-1,b,r),  d_y F(a,b,r) = F(a,b-1,r),
+//   d_z F(a,b,1) = F(a,b,0),    d_z F(a,b,0) = -F(a-2,b,1) - F(a,b-2,1),
+// so the gradient of order l is entries of order l - 1, and by Euler's identity
+// l F = eta . grad F gives order l.
+__host__ __device__ constexpr int horder(int a, int b, int r) { return b + r == 0 ? 0 : 2 * (b + r) - 1 + r; }
+
+// component (a, b, r) of the order held in F, zero where an index is negative
+__device__ __forceinline__ double hat(const double *F, int a, int b, int r)
+{
+    return a < 0 || b < 0 ? 0.0 : F[horder(a, b, r)];
+}
+
+// d_z of component (a, b, r), from the entries F of one order less, and whether
+// it has any term
+__host__ __device__ constexpr bool hat_dz_any(int a, int b, int r)
+{
+    return a >= 0 && b >= 0 && (r || a >= 2 || b >= 2);
+}
+__device__ __forceinline__ double hat_dz(const double *F, int a, int b, int r)
+{
+    if (a < 0 || b < 0) return 0.0;
+    if (r) return F[horder(a, b, 0)];
+    if (a < 2) return -hat(F, a, b - 2, 1);
+    if (b < 2) return -hat(F, a - 2, b, 1);
+    return -(hat(F, a - 2, b, 1) + hat(F, a, b - 2, 1));
+}
+
+// P2M of harmonic rows.  A particle's row, G_n = sum_sigma S_sigma
+// zeta^(n-sigma)/(n-sigma)! folded, has the same derivatives as F and degree
+// l - k for a source of order k: (l - k) G_l = zeta . grad G_l, from G_k = the
+// folded source tensor.  So every source order costs four multiply-adds a
+// component, and no table of powers, full row or fold is left.  A lane owns a
+// particle; the matrix unit sums the lanes: v_mfma_f64_4x4x4 adds, for its row
+// i, sum_k A[i][k] B[k][j] over lanes j + 4b + 16k, and with A one in row h % 4
+// and zero elsewhere component h of 16 particle groups lands in row h % 4 of
+// accumulator h / 4, over all passes of a leaf; the 16 sums of a component are
+// added through LDS at the end.  One wavefront per leaf.  FP64 operations bound
+// it at high p.  2 x 10^6 quadrupoles, p 10: 566 -> 129 us; 10^6 dipoles, p 6: 136 ->
+// 46; 100k dipoles, p 10: 45 -> 19; 400k charges in leaves of 7, p 10, where most
+// lanes idle: 181 -> 148; one leaf of 1000 charges, p 10: 98 -> 35.
+template <int H0, int L>
+__device__ __forceinline__ void p2m_add(const double *G, const double *sel, double *acc)
+{
+#pragma unroll
+    for (int j = 0; j <= 2 * L; ++j) {
+        const int h = L * L + j - H0;
+        acc[h / 4] = __builtin_amdgcn_mfma_f64_4x4x4f64(sel[h % 4], G[j], acc[h / 4], 0, 0, 0);
+    }
+}
+
+// orders l.. <= p of a source of order K, F1 = order l - 1
+template <int K, int H0, int PB, int l>
+__device__ __forceinline__ void p2m_orders(const double *F1, double x, double y, double z, int p, const double *sel,
+                                           double *acc)
+{
+    if constexpr (l <= PB) {
+        if (l > p) return;
+        const double hx = x * (1.0 / (l - K)), hy = y * (1.0 / (l - K)), hz = z * (1.0 / (l - K));
+        double F0[2 * l + 1];
+#pragma unroll
+        for (int j = 0; j <= 2 * l; ++j) {
+            const int t = (j + 1) / 2, r = j == 0 ? 0 : j - (2 * t - 1), a = l - t, b = t - r;
+            double v = 0.0;
+            if (a >= 1) v = hx * hat(F1, a - 1, b, r);
+            if (b >= 1) v = fma(hy, hat(F1, a, b - 1, r), v);
+            if (hat_dz_any(a, b, r)) v = fma(hz, hat_dz(F1, a, b, r), v);
+            F0[j] = v;
+        }
+        p2m_add<H0, l>(F0, sel, acc);
+        p2m_orders<K, H0, PB, l + 1>(F0, x, y, z, p, sel, acc);
+    }
+}
+
+template <int K, int H0, int PB>
+__device__ __forceinline__ void p2m_source(const double *G, double x, double y, double z, int p, const double *sel,
+                                           double *acc)
+{
+    if constexpr (K <= PB) {
+        if (K > p) return;
+        p2m_add<H0, K>(G, sel, acc);
+        p2m_orders<K, H0, PB, K + 1>(G, x, y, z, p, sel, acc);
+    }
+}
+
+// p <= PB
+template <int MASK, int PB>
+__global__ __launch_bounds__(64) void p2m_harmonic_kernel(int p, const int32_t *__restrict__ leaves,
+                                                          const DevCell *__restrict__ cells, Geo g,
+                                                          const double *__restrict__ xs, int n,
+                                                          const double *__restrict__ mom_user,
+                                                          const int32_t *__restrict__ perm, double *__restrict__ mom64,
+                                                          float *__restrict__ mom32, int nhp, float *__restrict__ Mh32,
+                                                          double *__restrict__ Mh64)
+{
+    constexpr int W = mask_width(MASK), S = mask_min_order(MASK), H0 = hterms(S - 1);
+    constexpr int NG = (hterms(PB) - H0 + 3) / 4;
+    __shared__ double red[NG * 64];
+    const int lane = threadIdx.x;
+    const int c = leaves[blockIdx.x];
+    const DevCell cell = cells[c];
+    double z[3];
+    cell_center(cell, g.lo, g.h, z);
+    const double ir = 1.0 / cell_radius(cell.level, g.h);
+    double sel[4], acc[NG];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) sel[k] = (lane & 3) == k ? 1.0 : 0.0;
+#pragma unroll
+    for (int k = 0; k < NG; ++k) acc[k] = 0.0;
+    for (int base = 0; base < cell.count; base += 64) {
+        // lanes past the leaf's end add zeros
+        const bool on = base + lane < cell.count;
+        const size_t i = (size_t)cell.first + base + lane;
+        double x = 0.0, y = 0.0, w = 0.0, m[W];
+#pragma unroll
+        for (int k = 0; k < W; ++k) m[k] = 0.0;
+        if (on) {
+            const double *src = mom_user + (size_t)perm[i] * W;
+#pragma unroll
+            for (int k = 0; k < W; ++k) m[k] = src[k];
+            sort_moments(i, MASK, m, mom64, mom32);
+            x = (z[0] - xs[i]) * ir;
+            y = (z[1] - xs[(size_t)n + i]) * ir;
+            w = (z[2] - xs[2 * (size_t)n + i]) * ir;
+        }
+        int off = 0;
+        if constexpr (MASK & 1) {
+            const double G[1] = {m[off++]};
+            p2m_source<0, H0, PB>(G, x, y, w, p, sel, acc);
+        }
+        if constexpr (MASK & 2) {
+            const double G[3] = {-m[off] * ir, -m[off + 1] * ir, -m[off + 2] * ir};
+            off += 3;
+            p2m_source<1, H0, PB>(G, x, y, w, p, sel, acc);
+        }
+        if constexpr (MASK & 4) {
+            // S_m = Q_m / m!; (0,0,2) folds onto -(2,0,0) and -(0,2,0)
+            const double ir2 = ir * ir, zz = 0.5 * m[off + 5];
+            const double G[5] = {(0.5 * m[off] - zz) * ir2, m[off + 1] * ir2, m[off + 2] * ir2,
+                                 (0.5 * m[off + 3] - zz) * ir2, m[off + 4] * ir2};
+            off += 6;
+            p2m_source<2, H0, PB>(G, x, y, w, p, sel, acc);
+        }
+        if constexpr (MASK & 8) {
+            // S_m = -O_m / m!; (1,0,2) folds onto -(3,0,0) and -(1,2,0), (0,1,2)
+            // onto -(2,1,0) and -(0,3,0), (0,0,3) onto -(2,0,1) and -(0,2,1)
+            const double ir3 = -(ir * ir * ir), *o = m + off;
+            const double xzz = 0.5 * o[5], yzz = 0.5 * o[8], zzz = o[9] * (1.0 / 6);
+            const double G[7] = {(o[0] * (1.0 / 6) - xzz) * ir3, (0.5 * o[1] - yzz) * ir3, (0.5 * o[2] - zzz) * ir3,
+                                 (0.5 * o[3] - xzz) * ir3,       o[4] * ir3,               (o[6] * (1.0 / 6) - yzz) * ir3,
+                                 (0.5 * o[7] - zzz) * ir3};
+            p2m_source<3, H0, PB>(G, x, y, w, p, sel, acc);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < NG; ++k) red[k * 64 + lane] = acc[k];
+    __syncthreads();
+    const int nh = hterms(p) - H0;
+    for (int h = lane; h < nh; h += 64) {
+        // component h: 16 lanes of accumulator h / 4, from another one each
+        // lane so that they spread over the banks
+        double v = 0.0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v += red[h * 16 + ((k + h) & 15)];
+        if (Mh32) Mh32[(size_t)c * nhp + h] = (float)v;
+        Mh64[(size_t)c * nhp + h] = v;
+    }
+}
+
+template <int MASK, int PB>
+static void p2m_launch_harmonic(fmm_tree *t, const Geo &g, const HarmOut &ho, hipStream_t s)
+{
+    hipLaunchKernelGGL((p2m_harmonic_kernel<MASK, PB>), dim3((unsigned)t->nleaves), dim3(64), 0, s, t->p, t->d_leaves,
+                       t->d_cells, g, t->d_x, (int)t->ht.n, t->mom_user, t->d_perm, t->d_mom, t->d_mom32, ho.nhp,
+                       ho.h32, ho.h64);
+}
+
 template <int MASK>
 static void p2m_launch(fmm_tree *t, hipStream_t s)
 {
@@ -582,10 +723,18 @@ static void p2m_launch(fmm_tree *t, hipStream_t s)
     const int nmp = (nterms(t->p) - nterms(t->order - 1) + 3) / 4 * 4;
     float *m32 = t->prec == FMM_PREC_MIXED ? t->d_M32 : nullptr;
     const HarmOut ho = harm_out(t);
+    if (ho.h64) {
+        // registers and LDS by the highest order a kernel takes
+        if (t->p <= 4) p2m_launch_harmonic<MASK, 4>(t, g, ho, s);
+        else if (t->p <= 6) p2m_launch_harmonic<MASK, 6>(t, g, ho, s);
+        else if (t->p <= 8) p2m_launch_harmonic<MASK, 8>(t, g, ho, s);
+        else p2m_launch_harmonic<MASK, FMM_P_MAX>(t, g, ho, s);
+        return;
+    }
     if constexpr (!(MASK & 4) || (MASK & 8)) {
         hipLaunchKernelGGL(p2m_coef_kernel<MASK>, dim3((unsigned)t->nleaves), dim3(kP2MThreads), 0, s, t->p, nmp,
                            t->d_leaves, t->d_cells, g, t->d_x, (int)t->ht.n, t->mom_user, t->d_perm, t->d_mom,
-                           t->d_mom32, t->d_M64, m32, ho.nhp, ho.h32, ho.h64);
+                           t->d_mom32, t->d_M64, m32);
         return;
     }
     const int S = t->order;
@@ -594,7 +743,7 @@ static void p2m_launch(fmm_tree *t, hipStream_t s)
     hipLaunchKernelGGL(p2m_kernel<MASK>, dim3((unsigned)t->nleaves), dim3(kP2MThreads), 0, s, t->p, nmp, blk, nitems,
                        ngroups, t->d_leaves,
                        t->d_cells, g, t->d_x, (int)t->ht.n, t->mom_user, t->d_perm, t->d_mom, t->d_mom32,
-                       t->d_M64, m32, ho.nhp, ho.h32, ho.h64);
+                       t->d_M64, m32);
 }
 
 hipError_t launch_p2m(fmm_tree *t, hipStream_t s)
@@ -996,42 +1145,16 @@ __global__ __launch_bounds__(64) void l2p_kernel(int outputs, const int32_t *__r
     }
 }
 
-// Harmonic basis.  With F_h, h = (a, b, r), the fold of the row eta^n/n!, the
-// expansion is sum_h L~_h F_h, and the fold commutes with derivatives:
-//   d_x F(a,b,r) = F(a-1,b,r),  d_y F(a,b,r) = F(a,b-1,r),
-//   d_z F(a,b,1) = F(a,b,0),    d_z F(a,b,0) = -F(a-2,b,1) - F(a,b-2,1),
-// so the gradient of order l is entries of order l - 1, and Euler's identity
-// l F = eta . grad F gives order l itself, as it gives the potential of each
-// order from its field.  One pass over the row then reads every coefficient once
-// and has nothing to rebuild; the second derivatives come from order l - 2, and
+// Harmonic basis: the expansion is sum_h L~_h F_h (the functions of a harmonic
+// row, above P2M), the gradient of order l is entries of order l - 1, and Euler's
+// identity gives the next order, and the potential of each order from its field.
+// One pass over the row then reads every coefficient once and has nothing to
+// rebuild; the second derivatives come from order l - 2, and
 // zz = -xx - yy.  The sums over monomials read each coefficient four times from
 // LDS, which bound them: 2 x 10^6 targets, q 8: 475 -> 102 us; 10^6, q 5: 74 -> 33;
 // 100k, q 9: 59 -> 14.  With the gradient, 400k targets: q 4 48 -> 30 us, q 8 200 ->
 // 71, q 10 332 -> 148 (there the orders no longer fit the registers).  What bounds
 // it now: the FP64 operations at high q, the targets' own traffic at low q.
-__host__ __device__ constexpr int horder(int a, int b, int r) { return b + r == 0 ? 0 : 2 * (b + r) - 1 + r; }
-
-// component (a, b, r) of the order held in F, zero where an index is negative
-__device__ __forceinline__ double hat(const double *F, int a, int b, int r)
-{
-    return a < 0 || b < 0 ? 0.0 : F[horder(a, b, r)];
-}
-
-// d_z of component (a, b, r), from the entries F of one order less, and whether
-// it has any term
-__host__ __device__ constexpr bool hat_dz_any(int a, int b, int r)
-{
-    return a >= 0 && b >= 0 && (r || a >= 2 || b >= 2);
-}
-__device__ __forceinline__ double hat_dz(const double *F, int a, int b, int r)
-{
-    if (a < 0 || b < 0) return 0.0;
-    if (r) return F[horder(a, b, 0)];
-    if (a < 2) return -hat(F, a, b - 2, 1);
-    if (b < 2) return -hat(F, a - 2, b, 1);
-    return -(hat(F, a - 2, b, 1) + hat(F, a, b - 2, 1));
-}
-
 struct L2PSums {
     double ph, fx, fy, fz, gxx, gxy, gxz, gyy, gyz;
 };

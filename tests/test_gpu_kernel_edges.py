@@ -234,3 +234,26 @@ def test_l2p_edges(orc, ctx, p, s, n, ncrit, kind):
         ok &= within(G.cpu().numpy(), o[2], FP64, "G")
     t.close()
     assert ok
+
+
+# P2M of harmonic rows: every set of source orders, orders below and above the
+# source's (a mixed set with p under its highest order), the bounds of its
+# kernels' orders, leaves of one particle, of 64 (one pass), 65 and more
+@pytest.mark.parametrize("mask,p,n,ncrit,kind", [(1, 1, 130, 1, "plummer"), (2, 4, 500, 65, "uniform"), (4, 5, 520, 64, "uniform"),
+                                                 (8, 6, 600, 66, "plummer"), (3, 7, 900, 200, "uniform"), (5, 8, 700, 30, "plummer"),
+                                                 (6, 9, 700, 130, "uniform"), (9, 2, 400, 8, "uniform"), (10, 10, 600, 64, "plummer"),
+                                                 (12, 4, 500, 40, "uniform"), (7, 10, 900, 300, "uniform"), (15, 3, 500, 16, "plummer"),
+                                                 (11, 6, 500, 33, "uniform"), (13, 8, 500, 20, "plummer"), (14, 9, 500, 70, "uniform")])
+@pytest.mark.parametrize("prec", [FP64, MIXED])
+def test_p2m_edges(orc, ctx, mask, p, n, ncrit, kind, prec):
+    w = _workload(4900 + mask, 16 + mask, n, kind, p, ncrit)
+    print(f"[p2m] mask={mask} p={p} n={n} ncrit={ncrit} {kind} precision={prec}", flush=True)
+    t = fmm.Tree(ctx, to_dev(w.pos), ncrit, w.theta)
+    t.upward(w.order, to_dev(w.moments), p, prec)
+    phi, E = t.evaluate()
+    torch.cuda.synchronize()
+    ophi, oE = orc.Tree(w.pos, ncrit, w.theta).fmm(w.order, w.moments, p)[:2]
+    ok = within(phi.cpu().numpy(), ophi, prec, "phi", floor=PHI_FLOOR)
+    ok &= within(E.cpu().numpy(), oE, prec, "E")
+    t.close()
+    assert ok
