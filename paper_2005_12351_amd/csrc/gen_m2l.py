@@ -58,6 +58,19 @@ registers.  What bounds it now is the issue of the 4x4x1 instruction (6.5 to
 theta 0.5, p 10: 1.07 -> 0.81 ms a launch; 100k dipoles, theta 0.3, p 10:
 0.384 -> 0.373 ms.
 
+FP64 matrix cores.  For p - s of 8 and 9 the "_f64_h" kernels use
+v_mfma_f64_4x4x4_4b_f64, a product of four outputs by four inputs for sixteen
+targets: A[i][k] = D_{n_{4g+i}+m} is the same for all targets, so one operand,
+gathered from the class's row in LDS through a table of offsets (a zero where
+n + m is past the tensor), serves the four instructions of the tile's 64
+targets; B holds the multipoles, lane j + 16k the coefficients of target j,
+two neighbours a load, so a load touches 16 rows and not 64.  The next
+coefficients, and the next entry's rows, load while the current ones multiply.
+The instruction reaches 72 TFLOP/s alone, multiply-adds 60 with two waves a
+SIMD, and the vector form here 34 (scalar loads of the derivatives, row
+gathers); 12 % of the products are padding at p 10, s 1.  100k particles: dipoles,
+theta 0.3, p 10: 779 -> 664 us; charges, p 8: 518 -> 427; theta 0.5, p 10: 191 -> 170.
+
 Usage: python gen_m2l.py OUTDIR  -> OUTDIR/m2l_s{0,1,2}_{f32,f64}[_h].hip, m2l_s{0,1,2}_f32_hm.hip
 """
 import os
@@ -74,6 +87,7 @@ DEFAULTS = {"acc32": 128, "m32": 64, "acc64": 64, "m64": 32, "dgroup32": 32, "dg
 
 ROW_LINE = 32           # FP32 coefficients of a 128-byte line: the chunk of the matrix-core kernels
 NQ = ROW_LINE // 4      # its float4s
+GROUPS64 = 13           # groups of four outputs an FP64 matrix-core block holds
 
 
 def orders(p):
@@ -668,6 +682,213 @@ static int occ_{name}()
     return "\n".join(L) + "\n" + launcher, meta
 
 
+def mfma64_pays(p, s):
+    """FP64 harmonic contractions the matrix cores take: two blocks of outputs,
+    p - s = 8 and 9.  With fewer outputs one vector block holds them all and the
+    padding of the tiles costs more than the unit gives (100k particles, theta
+    0.5, p 7: 76 us vector, 89 matrix; p 6: 61 and 66; p 4: 35 and 40); with more
+    (p - s = 10) a third block reads the rows again, and two blocks of 16 groups
+    leave no registers (10k: 75.5 us vector, 80 matrix; 300k: 887 and 944)."""
+    return 4 * GROUPS64 + 12 < len(reduced(orders(p - s))) <= 8 * GROUPS64
+
+
+def mfma64_blocks(p, s):
+    """Output blocks of the FP64 matrix-core kernels: ranges of groups of four
+    outputs, at most GROUPS64 (two accumulation registers a group and
+    sixteen targets)."""
+    ng = (len(reduced(orders(p - s))) + 3) // 4
+    nb = -(-ng // GROUPS64)
+    return [(ng * i // nb, ng * (i + 1) // nb) for i in range(nb)]
+
+
+def mfma64_steps(p, s, g0, g1):
+    """Tiles of a block in issue order: [(Q, e, [g, ...])].  Step (Q, e) multiplies
+    the coefficients 8Q + 2k + e, k = 0..3 (a lane loads two neighbours at once),
+    into the groups g that any of them reaches."""
+    ns = reduced(orders(p - s))
+    ms = reduced(orders(p)[nterms(s - 1):])
+    out = []
+    for Q in range((len(ms) + 7) // 8):
+        for e in (0, 1):
+            js = [8 * Q + 2 * k + e for k in range(4) if 8 * Q + 2 * k + e < len(ms)]
+            gs = [g for g in range(g0, g1)
+                  if any(sum(ns[i]) + sum(ms[j]) <= p for i in range(4 * g, min(len(ns), 4 * g + 4)) for j in js)]
+            if gs:
+                out.append((Q, e, gs))
+    return out
+
+
+def gen_kernel_mfma64(p, s, opt=None):
+    """FP64 harmonic contraction on the matrix cores (see the module's text)."""
+    opt = dict(DEFAULTS, **(opt or {}))
+    ns = reduced(orders(p - s))
+    ms = reduced(orders(p)[nterms(s - 1):])
+    nl, nm = len(ns), len(ms)
+    nlp, nmp, nd, scw = pad(nl, 4), pad(nm, 8), pad(nterms(p), 16), pad(p + 1, 4)
+    blocks = mfma64_blocks(p, s)
+    wgw = opt["wgw"]
+    NT = TILE * wgw
+    name = f"m2l_p{p}_s{s}_f64_h"
+    ND = -(-nd // TILE)          # derivative row: registers a lane
+    NS = -(-nmp // TILE)         # scale row
+    # byte offsets of the operand A of every tile: [tile / 4][lane % 4 + 4 (lane / 16)][tile % 4]
+    zero = nd
+    tab, first = [], []
+    for g0, g1 in blocks:
+        first.append(len(tab) // 64)
+        tiles = [(Q, e, g) for Q, e, gs in mfma64_steps(p, s, g0, g1) for g in gs]
+        for b in range(0, len(tiles), 4):
+            for pos in range(16):
+                i, kk = pos % 4, pos // 4
+                for x in range(4):
+                    off = zero
+                    if b + x < len(tiles):
+                        Q, e, g = tiles[b + x]
+                        j, n = 8 * Q + 2 * kk + e, 4 * g + i
+                        if j < nm and n < nl and sum(ns[n]) + sum(ms[j]) <= p:
+                            off = idx(tuple(a + c for a, c in zip(ns[n], ms[j])))
+                    tab.append(8 * off)
+    assert max(tab) < 65536
+    red = max(g1 - g0 for g0, g1 in blocks) * 4 * TILE
+    L = []
+    L.append(f"static __device__ const __align__(8) unsigned short tab_{name}[{len(tab)}] = {{{','.join(map(str, tab))}}};")
+    L.append(f"static __device__ const unsigned char ord_{name}[{nmp}] = "
+             f"{{{','.join(str(sum(ms[j])) if j < nm else '0' for j in range(nmp))}}};")
+    L.append(f"__global__ __launch_bounds__({NT}, 2) void {name}(M2LArgs a)")
+    L.append("{")
+    L.append(f"    __shared__ double red[{red}];")
+    L.append(f"    __shared__ double drow[{wgw}][{nd + 1}];")
+    L.append(f"    __shared__ __align__(16) double srow[{wgw}][{nmp}];")
+    L.append(f"    __shared__ __align__(16) unsigned short tab[{len(tab)}];")
+    L.append(f"    const int lane = threadIdx.x % {TILE};")
+    L.append(f"    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / {TILE});")
+    L.append("    const int col = lane & 15, kk = lane >> 4, pos = (lane & 3) + 4 * kk;")
+    L.append(f"    for (int i = threadIdx.x; i < {len(tab) // 4}; i += {NT}) ((ushort4 *)tab)[i] = ((const ushort4 *)tab_{name})[i];")
+    L.append(f"    if (lane == 0) drow[wv][{zero}] = 0.0;")
+    L.append("    __syncthreads();")
+    L.append("    const double *__restrict__ Mb = (const double *)a.M;")
+    L.append("    const double *__restrict__ Db = (const double *)a.D;")
+    L.append("    const double *__restrict__ Sb = (const double *)a.sc;")
+    L.append("    const char *const dl = (const char *)drow[wv];")
+    L.append("    const int p0 = a.wave_ptr[blockIdx.x], p1 = a.wave_ptr[blockIdx.x + 1];")
+    L.append("    for (int item = p0; item < p1; ++item) {")
+    L.append("    const int4 w = a.work[item];")
+    L.append("    const int blk = w.x >> 24;")
+    L.append(f"    double *__restrict__ out = (double *)a.part + (size_t)w.w * {nlp};")
+    L.append("    const int uspan = w.z - w.y;")
+    L.append(f"    const int ub = w.y + uspan * wv / {wgw}, ue = w.y + uspan * (wv + 1) / {wgw};")
+    SB = "            __builtin_amdgcn_sched_barrier(0);"
+
+    def rows(Q, suf, ptr):
+        return [f"            {'const ' if suf != 'N' else ''}{'double2 ' if suf != 'N' else ''}v{suf}_{x} = *(const double2 *)({ptr}{x} + {8 * Q});"
+                for x in range(4)]
+
+    for bi, (g0, g1) in enumerate(blocks):
+        steps = mfma64_steps(p, s, g0, g1)
+        L.append(f"    {'if' if bi == 0 else 'else if'} (blk == {bi}) {{")
+        for g in range(g0, g1):
+            L.append("        double " + ", ".join(f"c{g}_{x} = 0" for x in range(4)) + ";")
+        L.append("        if (ub < ue) {")
+        # the first entry's operands
+        L.append("        double2 vN_0, vN_1, vN_2, vN_3;")
+        L.append(f"        double dn[{ND}], sn[{NS}];")
+
+        def fetch_src(u):
+            return [f"            const double *r{x} = Mb + (size_t)a.usrc[(size_t){u} * {TILE} + {16 * x} + col] * {nmp} + 2 * kk;"
+                    for x in range(4)]
+
+        def fetch_rows(u):
+            o = [f"            const int cls = a.ucls[{u}];"]
+            for x in range(ND):
+                o.append(f"            dn[{x}] = Db[(size_t)cls * {nd} + min(lane + {TILE * x}, {nd - 1})];")
+            for x in range(NS):
+                o.append(f"            sn[{x}] = Sb[(size_t)cls * {scw} + ord_{name}[min(lane + {TILE * x}, {nmp - 1})]];")
+            return o
+
+        L.append("        {")
+        L.extend(fetch_src("ub"))
+        L.extend(rows(steps[0][0], "N", "r"))
+        L.extend(fetch_rows("ub"))
+        L.append("        }")
+        L.append("        for (int u = ub; u < ue; ++u) {")
+        # this entry's rows to LDS: the wave's own, in order with its reads
+        L.append("            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, \"wavefront\");")
+        L.append("            __builtin_amdgcn_wave_barrier();")
+        for x in range(ND):
+            c = f"if (lane + {TILE * x} < {nd}) " if TILE * (x + 1) > nd else ""
+            L.append(f"            {c}drow[wv][lane + {TILE * x}] = dn[{x}];")
+        for x in range(NS):
+            c = f"if (lane + {TILE * x} < {nmp}) " if TILE * (x + 1) > nmp else ""
+            L.append(f"            {c}srow[wv][lane + {TILE * x}] = sn[{x}];")
+        L.append("            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, \"wavefront\");")
+        L.append("            __builtin_amdgcn_wave_barrier();")
+        L.append("            const int un = min(u + 1, ue - 1);   // the next entry (the last: itself again)")
+        L.extend(fetch_src("u"))
+        L.extend(x.replace("const double *r", "const double *q") for x in fetch_src("un"))
+        L.append("            {")
+        L.extend(fetch_rows("un"))
+        L.append("            }")
+        Qs = sorted(set(Q for Q, _, _ in steps))
+        L.extend(f"            const double2 v{Qs[0]}_{x} = vN_{x};" for x in range(4))
+        tile = 0
+        for Q in Qs:
+            nxt = Qs[Qs.index(Q) + 1] if Q != Qs[-1] else None
+            L.append(SB)
+            if nxt is not None:
+                L.extend(rows(nxt, str(nxt), "r"))
+            else:
+                L.extend(rows(Qs[0], "N", "q"))
+            L.append(f"            const double2 s{Q} = *(const double2 *)&srow[wv][{8 * Q} + 2 * kk];")
+            for _, e, gs in [st for st in steps if st[0] == Q]:
+                comp = "xy"[e]
+                for x in range(4):
+                    L.append(f"            const double b{Q}{comp}_{x} = v{Q}_{x}.{comp} * s{Q}.{comp};")
+                for g in gs:
+                    if tile % 4 == 0:
+                        L.append(f"            const ushort4 t{tile // 4} = *(const ushort4 *)&tab[{(first[bi] + tile // 4) * 64} + 4 * pos];")
+                    L.append(f"            const double a{tile} = *(const double *)(dl + t{tile // 4}.{'xyzw'[tile % 4]});")
+                    for x in range(4):
+                        L.append(f"            c{g}_{x} = __builtin_amdgcn_mfma_f64_4x4x4f64(a{tile}, b{Q}{comp}_{x}, c{g}_{x}, 0, 0, 0);")
+                    tile += 1
+        L.append("        }")
+        L.append("        }")
+        # the waves' sums, in wave order: row 4 (g - g0) + lane / 16, target 16 x + lane % 16
+        for q in range(wgw):
+            L.append(f"        if (wv == {q}) {{")
+            for g in range(g0, g1):
+                for x in range(4):
+                    slot = f"red[{(g - g0) * 4 * TILE} + kk * {TILE} + {16 * x} + col]"
+                    if q == 0:
+                        L.append(f"            {slot} = c{g}_{x};")
+                    elif q < wgw - 1:
+                        L.append(f"            {slot} += c{g}_{x};")
+                    else:
+                        L.append(f"            out[(size_t)({16 * x} + col) * {nlp} + {4 * g} + kk] = {slot} + c{g}_{x};")
+            L.append("        }")
+            L.append("        __syncthreads();")
+        L.append("    }")
+    L.append("    }")
+    L.append("}")
+    launcher = f"""
+static hipError_t launch_{name}(const M2LArgs &a, int nwaves, hipStream_t st)
+{{
+    hipLaunchKernelGGL({name}, dim3(nwaves), dim3({NT}), 0, st, a);
+    return hipGetLastError();
+}}
+
+static int occ_{name}()
+{{
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, {name}, {NT}, 0) != hipSuccess) return 1;
+    return per_cu > 0 ? per_cu : 1;
+}}
+"""
+    work = [16 * sum(len(gs) for _, _, gs in mfma64_steps(p, s, g0, g1)) for g0, g1 in blocks]
+    meta = dict(name=name, nl_pad=nlp, nm_pad=nmp, nd=nd, nblocks=len(blocks), scw=scw,
+                blo=[4 * g0 for g0, _ in blocks] + [nl], bfma=work)
+    return "\n".join(L) + "\n" + launcher, meta
+
+
 def gen_file(s, fp32, opt=None, harmonic=False, mfma=False):
     suf = ("f32" if fp32 else "f64") + ("_h" if harmonic else "") + ("m" if mfma else "")
     parts = ["// Generated by gen_m2l.py; do not edit.", "#include <algorithm>", '#include "fmm_internal.h"', ""]
@@ -694,7 +915,12 @@ static __device__ __forceinline__ void wait_copies()
 }""")
     metas = []
     for p in range(s + 1, P_MAX + 1):
-        code, meta = gen_kernel_mfma(p, s, opt) if mfma else gen_kernel(p, s, fp32, opt, harmonic)
+        if mfma:
+            code, meta = gen_kernel_mfma(p, s, opt)
+        elif harmonic and not fp32 and mfma64_pays(p, s):
+            code, meta = gen_kernel_mfma64(p, s, opt)
+        else:
+            code, meta = gen_kernel(p, s, fp32, opt, harmonic)
         parts.append(code)
         metas.append((p, meta))
     parts.append(f"bool m2l_lookup_s{s}_{suf}(int p, M2LVariant *v)")

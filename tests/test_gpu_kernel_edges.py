@@ -257,3 +257,21 @@ def test_p2m_edges(orc, ctx, mask, p, n, ncrit, kind, prec):
     ok &= within(E.cpu().numpy(), oE, prec, "E")
     t.close()
     assert ok
+
+
+# the FP64 M2L on the matrix cores (p - s of 8 and 9) beside the vector kernels on
+# both sides of its range; few entries a wave, many, and levels that differ
+@pytest.mark.parametrize("p,s", [(7, 0), (8, 0), (9, 0), (10, 0), (9, 1), (10, 1), (10, 2), (10, 3)])
+@pytest.mark.parametrize("n,ncrit,kind", [(150, 16, "uniform"), (900, 8, "uniform"), (1500, 12, "plummer")])
+def test_fp64_m2l_range(orc, ctx, p, s, n, ncrit, kind):
+    w = _workload(5000 + 10 * p + s, s, n, kind, p, ncrit)
+    print(f"[fp64 m2l] p={p} s={s} n={n} ncrit={ncrit} {kind}", flush=True)
+    t = fmm.Tree(ctx, to_dev(w.pos), ncrit, w.theta)
+    phi, E = t.run(s, to_dev(w.moments), p, FP64)
+    torch.cuda.synchronize()
+    assert t.info()["n_m2l"] > 0
+    ophi, oE = orc.Tree(w.pos, ncrit, w.theta).fmm(w.order, w.moments, p)[:2]
+    ok = within(E.cpu().numpy(), oE, FP64, "E")
+    ok &= within(phi.cpu().numpy(), ophi, FP64, "phi", floor=PHI_FLOOR)
+    t.close()
+    assert ok
