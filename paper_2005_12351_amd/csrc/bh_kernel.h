@@ -21,11 +21,10 @@
 // in LDS and each accepting lane only marks the place; when the places run out
 // every lane evaluates the lowest place it has marked, in rounds, as long as
 // most lanes take part.  A lane then still evaluates its own cells with the
-// same operations; its sums add up in another order (FP64).  From p 6 on
-// (10^6 Plummer dipoles, theta 0.6, p 6, MIXED: 3.75 -> 3.55 ms; 30 011 charges,
-// p 10: 1.41 -> 1.07 ms; below, the places cost more than they save: p 4, 100k
-// quadrupoles 0.76 -> 0.79 ms) and in the harmonic basis; otherwise each cell is
-// evaluated as it is accepted, its row through scalar loads.
+// same operations; its sums add up in another order (FP64).  The places cost
+// LDS and registers, which the M2P has to be long enough to repay: see
+// bh_places_from.  Otherwise each cell is evaluated as it is accepted, its row
+// through scalar loads.
 //
 // A small system fills few wavefronts and then waits for the longest: `split`
 // of them share a group of particles.  All walk the cells above level
@@ -73,6 +72,13 @@ __device__ __forceinline__ void wave_sync_bh()
 }
 
 // row places of a wave, and the lanes below which a round waits for more marks
+// lowest p from which cells wait in LDS (harmonic basis).  us with / without
+// places, theta 0.6, Plummer: MIXED p 6, 10^6 dipoles 3550 / 3750, p 4, 100k
+// quadrupoles 790 / 760; MIXED gradient p 8, 100k charges 2489 / 3278, but p 6,
+// 10^6 10588 / 7844; FP64 p 8 1752 / 2488, p 10, 300k dipoles 6701 / 22438, but p
+// 6, 10^6 7911 / 5876; FP64 gradient p 10, 30 011 charges 12002 / 13517, but p 8,
+// 100k 6003 / 5555.
+constexpr int bh_places_from(bool f32, bool grad) { return f32 ? (grad ? 8 : 6) : (grad ? 10 : 8); }
 constexpr int kSlots = 32;
 constexpr int kRoundLanes = 36;
 constexpr int kOwnLevel = 3;
@@ -91,7 +97,7 @@ template <int P, int S, typename T, bool H, bool GRAD>
 __global__ __launch_bounds__(64) void bh_kernel(BHArgs a)
 {
     constexpr bool F32 = sizeof(T) == 4;
-    constexpr bool PLACES = H && P >= 6;
+    constexpr bool PLACES = H && P >= bh_places_from(sizeof(T) == 4, GRAD);
     constexpr int W = (S + 1) * (S + 2) / 2;
     __shared__ int stk_c[kStack];
     __shared__ unsigned long long stk_m[kStack];
