@@ -91,7 +91,7 @@ hipError_t launch_bh(fmm_tree *t, int outputs, double *phi, double *field, doubl
     a.mask = t->smask;
     a.w = mask_width(t->smask);
     a.grad = grad;
-    a.split = bh_split(t->ht.n);
+    a.split = t->d_bhpart ? bh_split(t->ht.n) : 1;
     a.part = t->d_bhpart;
     hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, s, t->d_bhcount, 2);
     hipLaunchKernelGGL(k, dim3((unsigned)((t->ht.n + 63) / 64) * a.split), dim3(64), 0, s, a);

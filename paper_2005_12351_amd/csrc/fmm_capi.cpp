@@ -810,10 +810,6 @@ static int ensure_expansions(fmm_tree *t, int code, int p, int prec)
     if (t->method == FMM_METHOD_BH && !t->d_bhcount &&
         (rc = tree_alloc(t, (void **)&t->d_bhcount, 2 * sizeof(unsigned long long))))
         return rc;
-    // (here, not in the evaluation, which allocates nothing)
-    if (t->method == FMM_METHOD_BH && !t->d_bhpart && bh_part_doubles(n) &&
-        (rc = tree_alloc(t, (void **)&t->d_bhpart, sizeof(double) * bh_part_doubles(n))))
-        return rc;
     if (!fmm && harm) {
         // folded rows the Barnes-Hut M2P reads (FMM trees size them from the M2L variant below)
         const size_t es = prec == FMM_PREC_MIXED ? sizeof(float) : sizeof(double);
@@ -901,6 +897,12 @@ static int ensure_expansions(fmm_tree *t, int code, int p, int prec)
     if (e == hipSuccess && t->d_M32)
         e = launch_fill((double *)t->d_M32, (size_t)(nc + 1) * nmp / 2, t->ctx->stream);
     if (e != hipSuccess) FAIL(FMM_EDEVICE, "fill failed: %s", hipGetErrorString(e));
+    // (here, not in the evaluation, which allocates nothing; last, and only
+    // where it fits: without it each group of particles is one wavefront's)
+    if (t->method == FMM_METHOD_BH && !t->d_bhpart && bh_part_doubles(n)) {
+        const size_t bytes = sizeof(double) * bh_part_doubles(n), limit = t->ctx->tree_limit;
+        if (!limit || t->dev_bytes + bytes <= limit) (void)tree_alloc(t, (void **)&t->d_bhpart, bytes);
+    }
     t->order = order;
     t->smask = smask;
     t->p = p;

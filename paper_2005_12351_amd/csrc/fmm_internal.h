@@ -315,7 +315,7 @@ struct fmm_tree {
     M2LWork m2lwork;
     double *d_cls_geom = nullptr;
     unsigned long long *d_bhcount = nullptr;   // Barnes-Hut interaction counters (2)
-    double *d_bhpart = nullptr;            // sums of wavefronts that share a group (bh_part_doubles)
+    double *d_bhpart = nullptr;            // sums of wavefronts that share a group (bh_part_doubles; null: none share)
     // per expansion state
     int have_up = 0, order = 0, p = 0, prec = 0, dtab_p = -1;   // order: the lowest source order s
     int smask = 1;                         // source orders present (bit mask)

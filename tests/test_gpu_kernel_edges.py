@@ -275,3 +275,25 @@ def test_fp64_m2l_range(orc, ctx, p, s, n, ncrit, kind):
     ok &= within(phi.cpu().numpy(), ophi, FP64, "phi", floor=PHI_FLOOR)
     t.close()
     assert ok
+
+
+# a Barnes-Hut tree whose limit has no room for the shared groups' sums: the call
+# is accepted as it is without them, and gives the same sums in another order
+def test_barnes_hut_without_share_scratch():
+    n, p = 3001, 7
+    w = _workload(5200, 1, n, "plummer", p, 32)
+    pos, mom = to_dev(w.pos), to_dev(w.moments)
+    out = []
+    for cut in (0, 1):
+        c = fmm.Context(0)
+        if cut:
+            c.set_tree_limit(out[0][2] - 1)   # one byte less than with the sums
+        t = fmm.Tree(c, pos, 32, 0.6, fmm.FMM_METHOD_BH)
+        t.upward(1, mom, p, FP64)
+        phi, E = t.evaluate()
+        torch.cuda.synchronize()
+        out.append((phi.cpu().numpy(), E.cpu().numpy(), t.info()["bytes"]))
+        t.close()
+        c.close()
+    assert out[1][2] < out[0][2]
+    assert within(out[1][0], out[0][0], FP64, "phi", floor=PHI_FLOOR) & within(out[1][1], out[0][1], FP64, "E")
