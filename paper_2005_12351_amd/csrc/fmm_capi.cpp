@@ -448,22 +448,26 @@ hipError_t ctx_pinned(fmm_ctx *ctx, size_t bytes, char **base)
 // sets the pointers and records ev_upload after it (the next use of the
 // pinned buffer waits for that event).  A copy costs about as much as a small
 // kernel's launch whatever its size: five vectors in one took 40 us off a
-// build.  Every vector passed to add() must live, unchanged, until flush()
-// returns; *block is the allocation (the pointers lie inside it).
+// build.  The vectors lie back to back, each at a multiple of its elements'
+// alignment, so with the wider elements added first the block holds nothing
+// but their bytes: a tree limit counts it.  Every vector passed to add() must
+// live, unchanged, until flush() returns; *block is the allocation (the
+// pointers lie inside it).
 struct Uploads {
     fmm_tree *t;
     struct Item {
         void **dst;
         const void *src;
-        size_t bytes;
+        size_t bytes, at;
     };
     std::vector<Item> items;
     size_t total = 0;
     template <typename T>
     void add(T **dst, const std::vector<T> &src)
     {
-        items.push_back(Item{(void **)dst, src.data(), src.size() * sizeof(T)});
-        total += std::max<size_t>(256, (src.size() * sizeof(T) + 255) / 256 * 256);
+        const size_t at = (total + alignof(T) - 1) / alignof(T) * alignof(T), bytes = src.size() * sizeof(T);
+        items.push_back(Item{(void **)dst, src.data(), bytes, at});
+        total = at + bytes;
     }
     int flush(hipStream_t s, void **block)
     {
@@ -473,13 +477,11 @@ struct Uploads {
         if (rc) return rc;
         char *base;
         HIPCHK(ctx_pinned(t->ctx, total, &base));
-        size_t o = 0;
         for (const Item &it : items) {
-            if (it.bytes) memcpy(base + o, it.src, it.bytes);
-            *it.dst = (char *)*block + o;
-            o += std::max<size_t>(256, (it.bytes + 255) / 256 * 256);
+            if (it.bytes) memcpy(base + it.at, it.src, it.bytes);
+            *it.dst = (char *)*block + it.at;
         }
-        HIPCHK(hipMemcpyAsync(*block, base, total, hipMemcpyHostToDevice, s));
+        if (total) HIPCHK(hipMemcpyAsync(*block, base, total, hipMemcpyHostToDevice, s));
         HIPCHK(hipEventRecord(t->ctx->ev_upload, s));
         t->ctx->upload_pending = true;
         items.clear();
@@ -713,23 +715,23 @@ extern "C" int fmm_build_tree(fmm_ctx *ctx, const double *pos, int64_t n, int nc
     HostScope hs_up(ctx, "host:tree_upload");
     int rc = FMM_OK;
     Uploads up{t};
+    std::vector<int32_t> cell_slot;   // lives until the flush below
+    if (method == FMM_METHOD_FMM && !t->tiling.on_device) {
+        const M2LTiling &tl = t->tiling;
+        up.add(&t->d_usrc, tl.usrc);   // rows of 64: the geometries after them stay aligned
+        up.add(&t->d_cls_geom, tl.cls_geom);
+        up.add(&t->d_ucls, tl.ucls);
+        cell_slot.assign(nc, -1);
+        for (size_t k = 0; k < tl.tile_cell.size(); ++k)
+            if (tl.tile_cell[k] >= 0) cell_slot[tl.tile_cell[k]] = (int32_t)k;
+        up.add(&t->d_cell_slot, cell_slot);
+    }
     up.add(&t->d_leaves, t->leaves);
     up.add(&t->d_nonleaf, t->level_nonleaf);
     up.add(&t->d_p2p_ptr, pptr);
     if (dev_src) t->d_p2p_src = dt.p2p_src;
     else up.add(&t->d_p2p_src, psrc);
     up.add(&t->d_p2p_order, p2p_order);
-    std::vector<int32_t> cell_slot;   // lives until the flush below
-    if (method == FMM_METHOD_FMM && !t->tiling.on_device) {
-        const M2LTiling &tl = t->tiling;
-        up.add(&t->d_ucls, tl.ucls);
-        up.add(&t->d_usrc, tl.usrc);
-        cell_slot.assign(nc, -1);
-        for (size_t k = 0; k < tl.tile_cell.size(); ++k)
-            if (tl.tile_cell[k] >= 0) cell_slot[tl.tile_cell[k]] = (int32_t)k;
-        up.add(&t->d_cell_slot, cell_slot);
-        up.add(&t->d_cls_geom, tl.cls_geom);
-    }
     if (method == FMM_METHOD_FMM) t->work[0] = (double)t->tiling.pairs;
     void *block;   // held until the tree is destroyed
     if ((rc = up.flush(s, &block)) || (rc = tree_alloc(t, (void **)&t->d_x, sizeof(double) * 3 * n))) {

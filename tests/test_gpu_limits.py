@@ -1,0 +1,39 @@
+"""Device memory against a tree limit: what a set-up may hold, and calls that a
+limit allows by what their result needs."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():  # pragma: no cover
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2005_12351_amd import fmm  # noqa: E402
+from paper_2005_12351_amd import workloads as W  # noqa: E402
+from tests.gpu_helpers import PHI_FLOOR, to_dev, within  # noqa: E402
+
+FP64, MIXED = fmm.FMM_PREC_FP64, fmm.FMM_PREC_MIXED
+
+
+# the host-made tables of a tree count with their own bytes: a system of one
+# cell and one of a few hundred in the bytes that each took with every table an
+# allocation of its own (dipoles, p 4, MIXED, harmonic basis; FMM)
+@pytest.mark.parametrize("n,where,build,total", [(1, fmm.FMM_SCHEDULE_DEVICE, 180, 9960), (1, fmm.FMM_SCHEDULE_HOST, 176, 9956),
+                                                 (300, fmm.FMM_SCHEDULE_DEVICE, 121860, 1714708),
+                                                 (300, fmm.FMM_SCHEDULE_HOST, 112780, 1705628)])
+def test_tables_count_their_own_bytes(n, where, build, total):
+    w = W.small_random(3, n, 1, "uniform", p=4, theta=0.5, ncrit=32)
+    pos, mom = to_dev(w.pos), to_dev(w.moments)
+    c = fmm.Context(0)
+    c.set_m2l_schedule(where)
+    c.set_tree_limit(total)
+    t = fmm.Tree(c, pos, 32, 0.5)
+    assert t.info()["bytes"] <= build
+    t.upward(1, mom, 4, MIXED)
+    assert t.info()["bytes"] <= total
+    phi, E = t.evaluate()
+    torch.cuda.synchronize()
+    assert torch.isfinite(phi).all() and torch.isfinite(E).all()
+    t.close()
+    c.close()
