@@ -823,44 +823,6 @@ static int ensure_expansions(fmm_tree *t, int code, int p, int prec)
         if ((rc = alloc_state(nhp))) return rc;
     }
     if (fmm) {
-        M2LVariant v;
-        if (!m2l_lookup(p, order, prec == FMM_PREC_MIXED, harm, &v, mfma))
-            FAIL(FMM_EINVAL, "no M2L kernel for p=%d s=%d", p, order);
-        const size_t es = prec == FMM_PREC_MIXED ? sizeof(float) : sizeof(double);
-        const int nc_ = std::max(1, t->tiling.nclasses);
-        const int scw = (p + 1 + 3) / 4 * 4;
-        // one wave per resident slot of the device
-        const int ncu = t->ctx->ncu;
-        // one M2L workgroup per resident workgroup slot; each writes its own
-        // partial rows where its piece of the work ends
-        build_m2l_work(t->tiling, v, ncu * v.occupancy(), t->m2lwork);
-        work.resize(t->m2lwork.work.size() / 4);
-        for (size_t k = 0; k < work.size(); ++k)
-            work[k] = make_int4(t->m2lwork.work[4 * k], t->m2lwork.work[4 * k + 1], t->m2lwork.work[4 * k + 2],
-                                t->m2lwork.work[4 * k + 3]);
-        up.add(&t->d_work, work);
-        up.add(&t->d_tile_chunk0, t->m2lwork.chunk0);
-        up.add(&t->d_tile_nchunk, t->m2lwork.nchunk);
-        up.add(&t->d_wave_ptr, t->m2lwork.wave_ptr);
-        if ((rc = tree_alloc(t, &t->d_part, es * (size_t)std::max<int64_t>(1, t->m2lwork.nrows) * v.nl_pad)) ||
-            (rc = tree_alloc(t, (void **)&t->d_L64, sizeof(double) * nc * (harm ? hterms(p - order) : nl))) ||
-            (rc = tree_alloc(t, (void **)&t->d_D64, sizeof(double) * nc_ * v.nd)) ||
-            (rc = tree_alloc(t, (void **)&t->d_D32, sizeof(float) * nc_ * v.nd)) ||
-            (rc = tree_alloc(t, (void **)&t->d_sc64, sizeof(double) * nc_ * scw)) ||
-            (rc = tree_alloc(t, (void **)&t->d_sc32, sizeof(float) * nc_ * scw)))
-            return rc;
-        // reduced multipole rows, plus the zero row that padded slots read
-        // (the M2L variant fixes the row stride: the matrix-core kernels
-        // align every row to a 128-byte cache line)
-        t->nhp = v.nm_pad;
-        if (harm && (rc = tree_alloc(t, &t->d_Mh, es * (size_t)(nc + 1) * v.nm_pad))) return rc;
-        if (harm) {
-            hipError_t e = launch_fill((double *)t->d_Mh, es * (size_t)(nc + 1) * v.nm_pad / 8, t->ctx->stream);
-            if (e != hipSuccess) FAIL(FMM_EDEVICE, "fill failed: %s", hipGetErrorString(e));
-            if ((rc = alloc_state(v.nm_pad))) return rc;
-        }
-    }
-    if (t->method == FMM_METHOD_FMM) {
         // L2P waves: consecutive leaves while they hold at most 64 particles
         // together and no more than the kernel takes (a larger leaf gets a wave of
         // its own)
@@ -889,8 +851,57 @@ static int ensure_expansions(fmm_tree *t, int code, int p, int prec)
                 pack_cols.size() < pack.size() || l2p_columns_pay(q, (int)pack.size() - 1, t->ctx->ncu);
             if (t->l2p_columns) pack.swap(pack_cols);
         }
-        up.add(&t->d_l2p_pack, pack);
         t->l2p_npacks = (int)pack.size() - 1;
+    }
+    if (fmm) {
+        M2LVariant v;
+        if (!m2l_lookup(p, order, prec == FMM_PREC_MIXED, harm, &v, mfma))
+            FAIL(FMM_EINVAL, "no M2L kernel for p=%d s=%d", p, order);
+        const size_t es = prec == FMM_PREC_MIXED ? sizeof(float) : sizeof(double);
+        const int nc_ = std::max(1, t->tiling.nclasses);
+        const int scw = (p + 1 + 3) / 4 * 4;
+        // one M2L workgroup per resident workgroup slot of the device; each
+        // writes its own partial rows where its piece of the work ends.  Where
+        // the tree limit has no room for the rows of that many pieces, half as
+        // many are tried (the sums are then of longer pieces).
+        const int slots = t->ctx->ncu * v.occupancy();
+        const size_t limit = t->ctx->tree_limit, nc1 = (size_t)nc + 1;
+        const size_t rows = harm ? nc1 * v.nm_pad * (prec == FMM_PREC_MIXED ? 4 + 8 : 8) : 0;   // d_Mh, d_Mf64
+        const size_t others = t->dev_bytes + rows + 8 * (size_t)nc * (harm ? hterms(p - order) : nl) +
+                              (8 + 4) * (size_t)nc_ * (v.nd + scw) + 4 * pack.size();
+        auto fits = [&] {
+            const M2LWork &wk = t->m2lwork;
+            return !limit || others + es * (size_t)std::max<int64_t>(1, wk.nrows) * v.nl_pad +
+                                     4 * (wk.work.size() + wk.chunk0.size() + wk.nchunk.size() + wk.wave_ptr.size()) <= limit;
+        };
+        build_m2l_work(t->tiling, v, slots, t->m2lwork);
+        if (!fits()) build_m2l_work(t->tiling, v, std::max(1, slots / 2), t->m2lwork);
+        work.resize(t->m2lwork.work.size() / 4);
+        for (size_t k = 0; k < work.size(); ++k)
+            work[k] = make_int4(t->m2lwork.work[4 * k], t->m2lwork.work[4 * k + 1], t->m2lwork.work[4 * k + 2],
+                                t->m2lwork.work[4 * k + 3]);
+        up.add(&t->d_work, work);
+        up.add(&t->d_tile_chunk0, t->m2lwork.chunk0);
+        up.add(&t->d_tile_nchunk, t->m2lwork.nchunk);
+        up.add(&t->d_wave_ptr, t->m2lwork.wave_ptr);
+        up.add(&t->d_l2p_pack, pack);
+        if ((rc = tree_alloc(t, &t->d_part, es * (size_t)std::max<int64_t>(1, t->m2lwork.nrows) * v.nl_pad)) ||
+            (rc = tree_alloc(t, (void **)&t->d_L64, sizeof(double) * nc * (harm ? hterms(p - order) : nl))) ||
+            (rc = tree_alloc(t, (void **)&t->d_D64, sizeof(double) * nc_ * v.nd)) ||
+            (rc = tree_alloc(t, (void **)&t->d_D32, sizeof(float) * nc_ * v.nd)) ||
+            (rc = tree_alloc(t, (void **)&t->d_sc64, sizeof(double) * nc_ * scw)) ||
+            (rc = tree_alloc(t, (void **)&t->d_sc32, sizeof(float) * nc_ * scw)))
+            return rc;
+        // reduced multipole rows, plus the zero row that padded slots read
+        // (the M2L variant fixes the row stride: the matrix-core kernels
+        // align every row to a 128-byte cache line)
+        t->nhp = v.nm_pad;
+        if (harm && (rc = tree_alloc(t, &t->d_Mh, es * (size_t)(nc + 1) * v.nm_pad))) return rc;
+        if (harm) {
+            hipError_t e = launch_fill((double *)t->d_Mh, es * (size_t)(nc + 1) * v.nm_pad / 8, t->ctx->stream);
+            if (e != hipSuccess) FAIL(FMM_EDEVICE, "fill failed: %s", hipGetErrorString(e));
+            if ((rc = alloc_state(v.nm_pad))) return rc;
+        }
     }
     if ((rc = up.flush(t->ctx->stream, &t->d_tables))) return rc;
     hipError_t e = t->d_M64 ? launch_fill(t->d_M64, (size_t)(nc + 1) * nmp, t->ctx->stream) : hipSuccess;

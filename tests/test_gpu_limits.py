@@ -37,3 +37,30 @@ def test_tables_count_their_own_bytes(n, where, build, total):
     assert torch.isfinite(phi).all() and torch.isfinite(E).all()
     t.close()
     c.close()
+
+
+# FP64 M2L of p - s 8 and 9: limits of what the trees held with the vector
+# kernels (rows of a multiple of four, their own cut of the work)
+@pytest.mark.parametrize("n,s,p,limit", [(100, 0, 9, None), (300, 0, 8, 17475176), (300, 0, 9, 20311404), (300, 2, 10, 18624648),
+                                         (3000, 0, 8, 24360672), (3000, 0, 9, 28383604), (3000, 1, 9, 25496400),
+                                         (3000, 1, 10, 29937364), (20000, 1, 9, 44753720)])
+def test_fp64_m2l_rows_fit_the_limit(orc, n, s, p, limit):
+    w = W.small_random(3, n, s, "uniform", p=4, theta=0.5, ncrit=32)
+    pos, mom = to_dev(w.pos), to_dev(w.moments)
+    out = []
+    for cut in (0, 1):
+        c = fmm.Context(0)
+        if cut:
+            c.set_tree_limit(limit or out[0][2] - 300)
+        t = fmm.Tree(c, pos, 32, 0.5)
+        t.upward(s, mom, p, FP64)
+        phi, E = t.evaluate()
+        torch.cuda.synchronize()
+        out.append((phi.cpu().numpy(), E.cpu().numpy(), t.info()["bytes"]))
+        t.close()
+        c.close()
+    ok = within(out[1][0], out[0][0], FP64, "phi", floor=PHI_FLOOR) & within(out[1][1], out[0][1], FP64, "E")
+    if n <= 3000:
+        po, Eo = orc.Tree(w.pos, 32, 0.5).fmm(s, w.moments, p)[:2]
+        ok &= within(out[1][0], po, FP64, "phi (oracle)", floor=PHI_FLOOR) & within(out[1][1], Eo, FP64, "E (oracle)")
+    assert ok
