@@ -525,6 +525,7 @@ extern "C" int fmm_build_tree(fmm_ctx *ctx, const double *pos, int64_t n, int nc
     HostScope hs_all(ctx, "host:build_tree");
     DevKeep dt;
     dt.keep = [t](void **p, size_t bytes) { return tree_alloc(t, p, bytes) == FMM_OK ? hipSuccess : hipErrorOutOfMemory; };
+    dt.drop = [t](void *p) { tree_free_block(t, p); };
     dt.tl = &t->tiling;
     // automatic: the device, measured faster than the host threads for
     // every tree from 3·10^3 list entries on (builds of 10^3 to 10^4

@@ -182,7 +182,8 @@ void host_parallel_for(int64_t n, const std::function<void(int64_t)> &f, int64_t
 // and the host tree holds none; tgt_top / src_top are the shallowest target
 // and source levels of the lists (-1: no list).
 struct DevKeep {
-    std::function<hipError_t(void **, size_t)> keep;
+    std::function<hipError_t(void **, size_t)> keep;   // memory of the tree
+    std::function<void(void *)> drop;                  // and back
     DevCell *cells = nullptr;
     int32_t *perm = nullptr;
     uint64_t *key = nullptr;

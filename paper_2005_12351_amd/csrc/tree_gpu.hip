@@ -1769,13 +1769,18 @@ hipError_t gpu_build_tree(const double *pos, int64_t n, int ncrit, double theta,
         if (tl.nclasses)
             GCHK(hipMemcpyAsync(dt.cls_geom, ts.geom, sizeof(double) * 4 * tl.nclasses, hipMemcpyDeviceToDevice, s));
     } else {
-        // the host makes the schedule, from its own copy of the M2L lists
+        // the host makes the schedule, from its own copy of the M2L lists: what
+        // the tree holds for the device's goes back
         std::vector<int32_t> hp((size_t)nc + 1), hsrc((size_t)n_m2l);
         GCHK(hipMemcpyAsync(hp.data(), mptr, sizeof(int32_t) * hp.size(), hipMemcpyDeviceToHost, s));
         if (n_m2l) GCHK(hipMemcpyAsync(hsrc.data(), msrc, sizeof(int32_t) * hsrc.size(), hipMemcpyDeviceToHost, s));
         GCHK(hipStreamSynchronize(s));
         t.m2l_ptr.assign(hp.begin(), hp.end());
         t.m2l_src.assign(hsrc.begin(), hsrc.end());
+        for (int32_t **p : {&dt.m2l_ptr, &dt.m2l_src, &dt.cell_slot}) {
+            if (*p) dt.drop(*p);
+            *p = nullptr;
+        }
         mark("host:tree_copy");
     }
     mark("host:tree_copyback");

@@ -64,3 +64,28 @@ def test_fp64_m2l_rows_fit_the_limit(orc, n, s, p, limit):
         po, Eo = orc.Tree(w.pos, 32, 0.5).fmm(s, w.moments, p)[:2]
         ok &= within(out[1][0], po, FP64, "phi (oracle)", floor=PHI_FLOOR) & within(out[1][1], Eo, FP64, "E (oracle)")
     assert ok
+
+
+# a tree whose M2L schedule the device gives up (more than 4096 pair geometries
+# in a tile): it holds what a tree with the host's schedule holds, fits its
+# limit and has the same schedule
+@pytest.mark.parametrize("n,ncrit,theta", [(3000, 4, 0.2)])
+def test_schedule_given_up_holds_what_the_host_s_does(n, ncrit, theta):
+    pos = torch.from_numpy(np.random.default_rng(5 + n).random((n, 3))).cuda()
+    dev, host = fmm.Context(0), fmm.Context(0)
+    host.set_m2l_schedule(fmm.FMM_SCHEDULE_HOST)
+    th = fmm.Tree(host, pos, ncrit, theta)
+    dev.set_tree_limit(th.info()["bytes"])
+    td = fmm.Tree(dev, pos, ncrit, theta)
+    a, b = td.m2l_schedule(), th.m2l_schedule()
+    assert a["where"] == b["where"] == fmm.FMM_SCHEDULE_HOST
+    assert td.info()["bytes"] == th.info()["bytes"]
+    for k in ("tile_cell", "tile_uoff", "ucls", "usrc", "cls_geom"):
+        assert np.array_equal(a[k], b[k]), k
+    x, y = td.export(), th.export()
+    for k in ("m2l_ptr", "m2l_src", "p2p_ptr", "p2p_src"):
+        assert np.array_equal(x[k], y[k]), k
+    for t in (td, th):
+        t.close()
+    dev.close()
+    host.close()
