@@ -1771,17 +1771,22 @@ hipError_t gpu_build_tree(const double *pos, int64_t n, int ncrit, double theta,
     } else {
         // the host makes the schedule, from its own copy of the M2L lists: what
         // the tree holds for the device's goes back
-        std::vector<int32_t> hp((size_t)nc + 1), hsrc((size_t)n_m2l);
-        GCHK(hipMemcpyAsync(hp.data(), mptr, sizeof(int32_t) * hp.size(), hipMemcpyDeviceToHost, s));
-        if (n_m2l) GCHK(hipMemcpyAsync(hsrc.data(), msrc, sizeof(int32_t) * hsrc.size(), hipMemcpyDeviceToHost, s));
+        // (the staging buffer is free again: what came through it is taken over)
+        const size_t o_src = al(sizeof(int32_t) * ((size_t)nc + 1));
+        GCHK(st.reserve(o_src + sizeof(int32_t) * (size_t)n_m2l));
+        GCHK(hipMemcpyAsync(st.base, mptr, sizeof(int32_t) * ((size_t)nc + 1), hipMemcpyDeviceToHost, s));
+        if (n_m2l)
+            GCHK(hipMemcpyAsync(st.base + o_src, msrc, sizeof(int32_t) * (size_t)n_m2l, hipMemcpyDeviceToHost, s));
         GCHK(hipStreamSynchronize(s));
-        t.m2l_ptr.assign(hp.begin(), hp.end());
-        t.m2l_src.assign(hsrc.begin(), hsrc.end());
+        mark("host:tree_copy");
+        const int32_t *hp = (const int32_t *)st.base, *hsrc = (const int32_t *)(st.base + o_src);
+        t.m2l_ptr.assign(hp, hp + nc + 1);
+        t.m2l_src.resize(n_m2l);
+        for (int64_t k = 0; k < n_m2l; ++k) t.m2l_src[k] = hsrc[k];
         for (int32_t **p : {&dt.m2l_ptr, &dt.m2l_src, &dt.cell_slot}) {
             if (*p) dt.drop(*p);
             *p = nullptr;
         }
-        mark("host:tree_copy");
     }
     mark("host:tree_copyback");
     return hipSuccess;
