@@ -255,6 +255,7 @@ struct BuildState {
     int64_t nm2l, np2p;                  // list lengths
     unsigned long long down;             // open-pair entries asked for
     unsigned long long info[6];          // schedule: targets, flags, entries, classes, shallowest target, source
+    unsigned long long longs;            // lists left unsorted: number << 40 | entries
     int32_t cursor, pad;                 // schedule: geometries of all tiles so far
 };
 
@@ -303,6 +304,7 @@ __global__ __launch_bounds__(256) void bbox_final_kernel(const double *__restric
     if (threadIdx.x == 0) {
         bs->nm2l = bs->np2p = 0;
         bs->down = 0;
+        bs->longs = 0;
         bs->cursor = 0;
     }
     double v[7];
@@ -742,9 +744,9 @@ __global__ __launch_bounds__(kListT) void lists_count_kernel(const DevCell *__re
     });
 }
 
-// ascending sort of v[0..n) by the workgroup (LDS or global memory): a
-// bitonic network whose comparators all point upwards, so that places past n
-// count as larger than everything and are left out
+// ascending sort of v[0..n) in LDS by the workgroup: a bitonic network whose
+// comparators all point upwards, so that places past n count as larger than
+// everything and are left out
 __device__ void block_sort(int32_t *v, int n)
 {
     int np = 1;
@@ -767,14 +769,23 @@ __device__ void block_sort(int32_t *v, int n)
 }
 
 // The lists of every cell, one workgroup each, sorted by source (already so
-// where the sources are all of one level: the order of the walk), in LDS or,
-// past its capacity, in place in the list itself.  With them the cell's
-// near-field cost (its particles times its P2P sources' particles) and its
-// M2L target key: level (5 bits) | octant (3) | lo0 hi0 lo1 hi1 lo2 hi2 (the
-// smallest and largest same-level source offset per axis, 7 bits each, + 64) |
-// 8191 - length (13); cells without an M2L list sort last.
+// where the sources are all of one level: the order of the walk), in LDS.  A
+// list past its capacity is written as it comes and, where that is not sorted,
+// left to sort_long_lists: its length and place go to `longs`, its number and
+// its first entry among all of them come from one atomic, so that the lists lie
+// in that array in the order of their entries.  With them the cell's near-field
+// cost (its particles times its P2P sources' particles) and its M2L target
+// key: level (5 bits) | octant (3) | lo0 hi0 lo1 hi1 lo2 hi2 (the smallest and
+// largest same-level source offset per axis, 7 bits each, + 64) | 8191 - length
+// (13); cells without an M2L list sort last.
 constexpr uint64_t kEmptyKey = ~0ull;
-constexpr int kM2LBuf = 3072, kP2PBuf = 1024;
+constexpr int kM2LBuf = 3072, kP2PBuf = 2048;
+constexpr int kLongShift = 40;
+struct LongList {
+    int32_t start, n;       // place in its array, length
+    uint32_t first;         // its first entry among all long lists
+    int32_t p2p;            // of the P2P lists, not the M2L lists
+};
 __global__ __launch_bounds__(kListT) void lists_emit_kernel(const DevCell *__restrict__ cells, double th2,
                                                             const uint2 *__restrict__ open_seg,
                                                             const uint32_t *__restrict__ open_buf,
@@ -782,13 +793,13 @@ __global__ __launch_bounds__(kListT) void lists_emit_kernel(const DevCell *__res
                                                             const int32_t *__restrict__ p2p_ptr, BuildState *bs,
                                                             int32_t *__restrict__ m2l_src, int32_t *__restrict__ p2p_src,
                                                             int64_t *__restrict__ cost, uint64_t *__restrict__ key,
-                                                            int32_t *__restrict__ val)
+                                                            int32_t *__restrict__ val, LongList *__restrict__ longs)
 {
     __shared__ ListShared ls;
     __shared__ int32_t mbuf[kM2LBuf], pbuf[kP2PBuf];
     __shared__ uint32_t root;
     __shared__ long long s_cost;
-    __shared__ int s_lo[3], s_hi[3];
+    __shared__ int s_lo[3], s_hi[3], s_first;
     const int B = blockIdx.x;
     const DevCell b = cells[B];
     const int m0 = m2l_ptr[B], mn = m2l_ptr[B + 1] - m0, p0 = p2p_ptr[B], pn = p2p_ptr[B + 1] - p0;
@@ -798,6 +809,7 @@ __global__ __launch_bounds__(kListT) void lists_emit_kernel(const DevCell *__res
     if (threadIdx.x == 0) {
         root = 0;
         s_cost = 0;
+        s_first = INT_MAX;
     }
     if (threadIdx.x < 3) {
         s_lo[threadIdx.x] = INT_MAX;
@@ -822,15 +834,22 @@ __global__ __launch_bounds__(kListT) void lists_emit_kernel(const DevCell *__res
         });
     }
     __syncthreads();
-    auto finish = [&](int32_t *v, int n, int32_t *out) {
+    auto finish = [&](int32_t *v, int n, int32_t *out, int start, int p2p) {
         int bad = 0;
         for (int k = threadIdx.x; k + 1 < n; k += kListT) bad |= v[k] > v[k + 1];
-        if (__syncthreads_or(bad)) block_sort(v, n);
+        if (__syncthreads_or(bad)) {
+            if (v != out) {
+                block_sort(v, n);
+            } else if (threadIdx.x == 0) {
+                const unsigned long long at = atomicAdd(&bs->longs, 1ull << kLongShift | (unsigned long long)n);
+                longs[at >> kLongShift] = LongList{start, n, (uint32_t)at, p2p};
+            }
+        }
         if (v != out)
             for (int k = threadIdx.x; k < n; k += kListT) out[k] = v[k];
     };
-    finish(mv, mn, m2l_src + m0);
-    finish(pv, pn, p2p_src + p0);
+    finish(mv, mn, m2l_src + m0, m0, 0);
+    finish(pv, pn, p2p_src + p0, p0, 1);
     __syncthreads();
     if (pn) {
         long long c = 0;
@@ -840,7 +859,9 @@ __global__ __launch_bounds__(kListT) void lists_emit_kernel(const DevCell *__res
     }
     int lo[3] = {INT_MAX, INT_MAX, INT_MAX}, hi[3] = {INT_MIN, INT_MIN, INT_MIN};
     if (key && mn) {
+        int first = INT_MAX;
         for (int k = threadIdx.x; k < mn; k += kListT) {
+            first = min(first, mv[k]);
             const DevCell A = cells[mv[k]];
             if (A.level != b.level) continue;
             const int o[3] = {A.ix - b.ix, A.iy - b.iy, A.iz - b.iz};
@@ -861,6 +882,8 @@ __global__ __launch_bounds__(kListT) void lists_emit_kernel(const DevCell *__res
                 atomicMax(&s_hi[d], hi[d]);
             }
         }
+        for (int w = 32; w > 0; w >>= 1) first = min(first, __shfl_xor(first, w, 64));
+        if ((threadIdx.x & 63) == 0) atomicMin(&s_first, first);
     }
     __syncthreads();
     if (threadIdx.x != 0) return;
@@ -889,11 +912,36 @@ __global__ __launch_bounds__(kListT) void lists_emit_kernel(const DevCell *__res
     k |= (uint64_t)(8191 - min(mn, 8191));
     key[B] = k;
     if (!ok) atomicOr(&bs->info[1], 1ull);   // a key field overflows
-    // shallowest levels (lists are sorted by source and cells are level-major);
-    // read first: few cells lower them
-    const unsigned long long tl = b.level, sl = cells[mv[0]].level;
+    // shallowest levels (cells are level-major); read first: few cells lower them
+    const unsigned long long tl = b.level, sl = cells[s_first].level;
     if (tl < __hip_atomic_load(&bs->info[4], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(&bs->info[4], tl);
     if (sl < __hip_atomic_load(&bs->info[5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(&bs->info[5], sl);
+}
+
+// entries of long lists [l0, l0 + gridDim.x): the key is the list's first entry
+// (after `base`) before the source, so one sort sorts every list in its place
+__global__ void long_keys_kernel(const LongList *__restrict__ longs, int l0, uint32_t base, int bits,
+                                 const int32_t *__restrict__ m2l_src, const int32_t *__restrict__ p2p_src,
+                                 uint64_t *__restrict__ key, int32_t *__restrict__ val)
+{
+    const int l = l0 + blockIdx.x;
+    const LongList L = longs[l];
+    const int32_t *src = (L.p2p ? p2p_src : m2l_src) + L.start;
+    const uint32_t f = L.first - base;
+    for (int k = blockIdx.y * blockDim.x + threadIdx.x; k < L.n; k += gridDim.y * blockDim.x) {
+        key[f + k] = (uint64_t)f << bits | (uint32_t)src[k];
+        val[f + k] = l;
+    }
+}
+
+__global__ void long_store_kernel(const LongList *__restrict__ longs, int n, uint32_t base, int bits,
+                                  const uint64_t *__restrict__ key, const int32_t *__restrict__ val,
+                                  int32_t *__restrict__ m2l_src, int32_t *__restrict__ p2p_src)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const LongList L = longs[val[i]];
+    (L.p2p ? p2p_src : m2l_src)[L.start + (i - (int)(L.first - base))] = (int32_t)(key[i] & ((1ull << bits) - 1));
 }
 
 __global__ void last_of_scans_kernel(int32_t *mptr, int32_t *pptr, int nc, const BuildState *bs)
@@ -1062,6 +1110,61 @@ hipError_t radix_sort(Dev &dv, uint64_t *&k, int32_t *&v, int n, int bits)
     return hipSuccess;
 }
 
+// The long lists lists_emit_kernel left unsorted (`nlong` of them, `total`
+// entries), by one radix sort of all their entries, kLongBatch at most at a
+// time (whole lists).  A workgroup that sorts its list in global memory keeps
+// the rest waiting: dense cores with a few far particles, 30 000 points (longest
+// list 18 085), lists and schedule 1.65 -> 0.53 ms; 1.2 million (109 719)
+// 11.1 -> 2.4.
+constexpr int64_t kLongBatch = 1 << 22;   // 150 MB of scratch
+hipError_t sort_long_lists(Dev &dv, const LongList *longs, int64_t nlong, int64_t total, int nc, int32_t *m2l_src,
+                           int32_t *p2p_src)
+{
+    hipStream_t s = dv.s;
+    // list ranges and first entries of the batches
+    std::vector<int64_t> l0{0, nlong}, e0{0, total};
+    int64_t cap = total;
+    if (total > kLongBatch) {
+        std::vector<LongList> h((size_t)nlong);
+        GCHK(hipMemcpyAsync(h.data(), longs, sizeof(LongList) * h.size(), hipMemcpyDeviceToHost, s));
+        GCHK(hipStreamSynchronize(s));
+        l0.assign(1, 0);
+        e0.assign(1, 0);
+        cap = 0;
+        for (int64_t l = 0; l < nlong; ++l)
+            if ((int64_t)h[l].first + h[l].n - e0.back() > kLongBatch && l > l0.back()) {
+                l0.push_back(l);
+                e0.push_back(h[l].first);
+            }
+        l0.push_back(nlong);
+        e0.push_back(total);
+        for (size_t k = 0; k + 1 < e0.size(); ++k) cap = std::max(cap, e0[k + 1] - e0[k]);
+        if (cap > INT32_MAX) return hipErrorOutOfMemory;
+    }
+    uint64_t *key = dv.alloc<uint64_t>(cap), *key2 = dv.alloc<uint64_t>(cap);
+    int32_t *val = dv.alloc<int32_t>(cap), *val2 = dv.alloc<int32_t>(cap);
+    size_t tb = 0;
+    auto width = [](int64_t v) { return 64 - __builtin_clzll((unsigned long long)v | 1); };
+    const int bits = width(nc - 1), all = bits + width(cap);
+    GCHK(dev_sort_pairs(nullptr, tb, key, key2, val, val2, (int)cap, all, s));
+    char *tmp = dv.alloc<char>(tb);
+    GCHK(dv.err);
+    for (size_t k = 0; k + 1 < l0.size(); ++k) {
+        const int n = (int)(e0[k + 1] - e0[k]);
+        for (int64_t l = l0[k]; l < l0[k + 1]; l += 32768)
+            hipLaunchKernelGGL(long_keys_kernel, dim3((unsigned)std::min<int64_t>(32768, l0[k + 1] - l), 16), dim3(256), 0, s,
+                               longs, (int)l, (uint32_t)e0[k], bits, (const int32_t *)m2l_src, (const int32_t *)p2p_src, key,
+                               val);
+        GCHK(hipGetLastError());
+        size_t tb2 = tb;
+        GCHK(dev_sort_pairs(tmp, tb2, key, key2, val, val2, n, all, s));
+        hipLaunchKernelGGL(long_store_kernel, dim3(nblk(n, 256)), dim3(256), 0, s, longs, n, (uint32_t)e0[k], bits,
+                           (const uint64_t *)key2, (const int32_t *)val2, m2l_src, p2p_src);
+        GCHK(hipGetLastError());
+    }
+    return hipSuccess;
+}
+
 // host staging of the device-to-host copies: the context's pinned buffer
 // (fast, asynchronous copies), grown on demand, or plain host memory
 struct Staging {
@@ -1193,7 +1296,8 @@ __global__ __launch_bounds__(kClsT) void tile_classes_kernel(const DevCell *__re
         }
         bad = 1;
     };
-    for (int e = e0 + part; e < e1; e += kClsT / 64) {
+    // (a tile given up is left at once: in a full table every look-up walks it all)
+    for (int e = e0 + part; e < e1 && !*(volatile int *)&bad; e += kClsT / 64) {
         uint64_t k;
         if (!pack_class(cells[src[e]], cb, k)) bad = 1;
         insert(k);
@@ -1725,12 +1829,13 @@ hipError_t gpu_build_tree(const double *pos, int64_t n, int ncrit, double theta,
         msrc = dv.alloc<int32_t>(n_m2l);
     }
     int64_t *cost = dv.alloc<int64_t>(nc);
+    LongList *longs = dv.alloc<LongList>((size_t)(n_m2l / kM2LBuf + n_p2p / kP2PBuf));
     uint64_t *tkey = tiling ? dv.alloc<uint64_t>(nc) : nullptr;
     int32_t *tval = tiling ? dv.alloc<int32_t>(nc) : nullptr;
     GCHK(dv.err);
     hipLaunchKernelGGL(lists_emit_kernel, dim3((unsigned)nc), dim3(kListT), 0, s, (const DevCell *)cells, th2,
                        (const uint2 *)open_seg, (const uint32_t *)open_buf, (const int32_t *)mptr, (const int32_t *)pptr,
-                       bs, msrc, psrc, cost, tkey, tval);
+                       bs, msrc, psrc, cost, tkey, tval, longs);
     GCHK(hipGetLastError());
     GCHK(hipMemcpyAsync(st.base + o_pp, pptr, sizeof(int32_t) * (nc + 1), hipMemcpyDeviceToHost, s));
     GCHK(hipMemcpyAsync(st.base + o_pk, cost, sizeof(int64_t) * nc, hipMemcpyDeviceToHost, s));
@@ -1744,6 +1849,10 @@ hipError_t gpu_build_tree(const double *pos, int64_t n, int ncrit, double theta,
     // the device works
     host_cells();
     GCHK(read_words(dv, bs, (int)(sizeof(BuildState) / 8), &hs));
+    // (the schedule does not depend on the order within a list)
+    if (hs.longs)
+        GCHK(sort_long_lists(dv, longs, (int64_t)(hs.longs >> kLongShift),
+                             (int64_t)(hs.longs & ((1ull << kLongShift) - 1)), nc, msrc, psrc));
     dt.done = false;
     if (tiling) GCHK(finish_tiling(dv, cells, nc, mptr, msrc, bs, hs.info, dt, ts));
     mark("host:tree_tiling");
