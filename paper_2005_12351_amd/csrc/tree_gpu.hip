@@ -1795,10 +1795,13 @@ hipError_t gpu_build_tree(const double *pos, int64_t n, int ncrit, double theta,
     // Open pairs a cell leaves to its children: those too near to be accepted,
     // 4/3 pi theta^-3 of its size (33 at theta 0.5), over the cells that split
     // (an eighth of a uniform tree's, more of a clustered one's); a margin
-    // over both (never more than every pair of cells; 256 MB at most at first),
+    // over both (never more than every pair of cells, and at first no more than a
+    // sixteenth of what the context may keep, 256 MB of the default budget),
     // and again with what was asked for where it does not do.
     const double rth = 0.5 / theta;
-    unsigned cap = (unsigned)std::min(20.0 * rth * rth * rth * nc + 65536.0, std::min((double)nc * nc + 1.0, 67108864.0));
+    unsigned cap = (unsigned)std::min(20.0 * rth * rth * rth * nc + 65536.0,
+                                      std::min((double)nc * nc + 1.0, (double)(ctx_cache_limit(ctx) / 16 / sizeof(uint32_t))));
+    cap = std::max(cap, 1u);
     uint32_t *open_buf = dv.alloc<uint32_t>(cap);
     GCHK(dv.err);
     for (;;) {

@@ -124,8 +124,8 @@ def _points(kind, n):
 
 # the tree and the lists against the oracle, whole numbers: workgroups of 256
 # particles (just below, at and above), windows beyond LDS (ncrit > 3840) and
-# beyond the input, one cell, a depth-cap chain, P2P lists beyond the LDS list
-# (1024) and the open pairs beyond theirs
+# beyond the input, one cell, a depth-cap chain, lists of several thousand P2P
+# sources (beyond LDS, with the open pairs: test_gpu_list_capacities)
 @pytest.mark.parametrize("kind,n,ncrit,theta", [("uniform", 255, 8, 0.5), ("uniform", 256, 256, 0.5),
                                                 ("uniform", 257, 256, 0.5), ("uniform", 513, 1, 0.6),
                                                 ("uniform", 9000, 4000, 0.5), ("uniform", 9000, 3840, 0.5),

@@ -47,3 +47,67 @@ def test_lists_beyond_lds(orc, kind, n, ncrit, theta, m2l, batches):
         _tree_equal(gt, o)
         gt.close()
         ctx.close()
+
+
+def _open_pairs(o, theta):
+    """pairs (source, target) that each target cell leaves open to its children: neither accepted nor of two leaves,
+    and split at the target"""
+    lev, ix = o.level.astype(np.int64), o.ix.astype(np.int64).reshape(-1, 3)
+    ch0, nch = o.child0.astype(np.int64), o.nchild.astype(np.int64)
+    count = np.zeros(len(lev), np.int64)
+    a = b = np.zeros(1, np.int64)
+
+    def split(x, y):
+        """x's children, each with its y"""
+        k = nch[x]
+        return np.repeat(ch0[x], k) + np.arange(k.sum()) - np.repeat(np.cumsum(k) - k, k), np.repeat(y, k)
+
+    while len(a):
+        ra, rb = 1 << (21 - lev[a]), 1 << (21 - lev[b])
+        d = (2 * ix[b] + 1) * rb[:, None] - (2 * ix[a] + 1) * ra[:, None]
+        near = ~((ra + rb).astype(float) ** 2 < theta * theta * (d.astype(float) ** 2).sum(1))
+        la, lb = nch[a] == 0, nch[b] == 0
+        rest = near & ~(la & lb)
+        source = rest & (lb | (~la & (ra > rb)))
+        target = rest & ~source
+        np.add.at(count, b[target], 1)
+        both = target & ~la & (ra == rb)
+        only = target & ~both
+        a1, b1 = split(a[source], b[source])
+        b2, a2 = split(b[only], a[only])
+        b3, a3 = split(b[both], a[both])
+        a3, b3 = split(a3, b3)
+        a, b = np.concatenate([a1, a2, a3]), np.concatenate([b1, b2, b3])
+    return count
+
+
+# a target with more open pairs than its LDS buffer takes walks twice
+def test_open_pairs_beyond_lds(orc):
+    n, ncrit, theta = 4100, 1, 0.1
+    pos = np.ascontiguousarray(_points("uniform", n))
+    print(f"[open pairs] n={n} ncrit={ncrit} theta={theta}", flush=True)
+    o = orc.Tree(pos, ncrit, theta).dump()
+    assert _open_pairs(o, theta).max() > OPEN_LDS
+    ctx = fmm.Context(0)
+    gt = fmm.Tree(ctx, torch.from_numpy(pos).cuda(), ncrit, theta)
+    _tree_equal(gt, o)
+    gt.close()
+    ctx.close()
+
+
+# a context whose budget leaves the open pairs' buffer fewer entries than they
+# need (1/512 of it in bytes) runs the levels again with more
+@pytest.mark.parametrize("kind,n,ncrit,theta,budget", [("uniform", 9000, 1, 0.5, 1 << 20), ("cluster", 4000, 4, 0.4, 1 << 16),
+                                                       ("same", 300, 3, 0.5, 1 << 10)])
+@pytest.mark.parametrize("where", [fmm.FMM_SCHEDULE_AUTO, fmm.FMM_SCHEDULE_HOST])
+def test_open_pairs_beyond_their_buffer(orc, kind, n, ncrit, theta, budget, where):
+    pos = np.ascontiguousarray(_points(kind, n))
+    print(f"[open buffer] {kind} n={n} ncrit={ncrit} theta={theta} budget={budget}", flush=True)
+    o = orc.Tree(pos, ncrit, theta).dump()
+    assert _open_pairs(o, theta).sum() > max(1, budget // 8 // 64)
+    ctx = fmm.Context(0, budget_bytes=budget)
+    ctx.set_m2l_schedule(where)
+    gt = fmm.Tree(ctx, torch.from_numpy(pos).cuda(), ncrit, theta)
+    _tree_equal(gt, o)
+    gt.close()
+    ctx.close()
