@@ -253,7 +253,10 @@ int fmm_ctx_set_overlap(fmm_ctx *ctx, int on);
  * fmm_evaluate is captured the second time a tree sees a given argument set
  * (moments / output pointers, order, p, precision; the first time it is
  * launched kernel by kernel) and replayed afterwards,
- * which removes the per-kernel launch cost.  Graphs are never used while
+ * which removes the per-kernel launch cost.  A tree remembers up to 64
+ * argument sets that it has launched once and then starts anew, so a program
+ * that goes through more of them in turn has its kernels launched one by one.
+ * Graphs are never used while
  * profiling is enabled.  Off: kernels are launched one by one. */
 int fmm_ctx_set_graphs(fmm_ctx *ctx, int on);
 
