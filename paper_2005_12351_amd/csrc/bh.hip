@@ -47,25 +47,27 @@ __global__ void bh_reduce_kernel(int n, int split, int no, int outputs, const do
 }  // namespace
 
 // Wavefronts a group of 64 particles: as many, up to eight, as keep them within
-// kBHWaves, one a SIMD (what fits of the kernels of the highest orders): they
-// all run side by side then and the launch takes as long as the longest.
+// one a SIMD (what fits of the kernels of the highest orders): they all run
+// side by side then and the launch takes as long as the longest.
 // Passes of 2001 Plummer dipoles, p 6: 569 -> 370 us; 5001 octupoles, FP64:
 // 707 -> 157; 30 011 charges, p 10 (two a group): 1067 -> 627.  With up to 3072
 // wavefronts the orders that fit one a SIMD queue for it and lose (30 011
 // dipoles, p 8, FP64: 1732 -> 2343 us; 1642 with this limit).
-constexpr int kBHWaves = 1024;
-int bh_split(int64_t n)
+static int bh_split(int64_t n, int ncu)
 {
     const int64_t groups = (n + 63) / 64;
     int k = 1;
-    while (k < 8 && 2 * k * groups <= kBHWaves) k *= 2;
+    while (k < 8 && 2 * k * groups <= 4 * ncu) k *= 2;
     return k;
 }
-size_t bh_part_doubles(int64_t n)
+// doubles of the sums of n particles, and the most any n takes: 64 particles a
+// wavefront, phi, E and the gradient
+size_t bh_part_doubles(int64_t n, int ncu)
 {
-    const int k = bh_split(n);
+    const int k = bh_split(n, ncu);
     return k > 1 ? (size_t)k * n * 10 : 0;
 }
+size_t bh_part_max(int ncu) { return (size_t)4 * ncu * 64 * 10; }
 
 hipError_t launch_bh(fmm_tree *t, int outputs, double *phi, double *field, double *grad, hipStream_t s)
 {
@@ -91,14 +93,14 @@ hipError_t launch_bh(fmm_tree *t, int outputs, double *phi, double *field, doubl
     a.mask = t->smask;
     a.w = mask_width(t->smask);
     a.grad = grad;
-    a.split = t->d_bhpart ? bh_split(t->ht.n) : 1;
-    a.part = t->d_bhpart;
+    a.part = t->d_bhpart ? t->d_bhpart : t->ctx->bh_part;
+    a.split = a.part ? bh_split(t->ht.n, t->ctx->ncu) : 1;
     hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, s, t->d_bhcount, 2);
     hipLaunchKernelGGL(k, dim3((unsigned)((t->ht.n + 63) / 64) * a.split), dim3(64), 0, s, a);
     if (a.split > 1) {
         const int no = (outputs & FMM_GRAD) ? 10 : 4;
         hipLaunchKernelGGL(bh_reduce_kernel, dim3((unsigned)((t->ht.n * no + 255) / 256)), dim3(256), 0, s, (int)t->ht.n,
-                           a.split, no, outputs, (const double *)t->d_bhpart, t->d_perm, phi, field, grad);
+                           a.split, no, outputs, (const double *)a.part, t->d_perm, phi, field, grad);
     }
     return hipGetLastError();
 }

@@ -344,6 +344,8 @@ extern "C" int fmm_ctx_destroy(fmm_ctx *c)
     }
     c->trees.clear();
     ctx_cache_drop(c);
+    if (c->bh_part) (void)hipFreeAsync(c->bh_part, c->stream);
+    c->bh_part = nullptr;
     if (c->arena) (void)hipFreeAsync(c->arena, c->stream);
     c->arena = nullptr;
     c->arena_cap = 0;
@@ -781,8 +783,8 @@ static int ensure_expansions(fmm_tree *t, int code, int p, int prec)
     std::vector<int32_t> pack;
     for (void **pp : {(void **)&t->d_mom, (void **)&t->d_mom32, (void **)&t->d_M64, (void **)&t->d_M32, &t->d_Mh,
                       (void **)&t->d_Mf64, (void **)&t->d_part, (void **)&t->d_L64, (void **)&t->d_near, (void **)&t->d_near_g,
-                      (void **)&t->d_D64,
-                      (void **)&t->d_D32, (void **)&t->d_sc64, (void **)&t->d_sc32, &t->d_tables}) {
+                      (void **)&t->d_D64, (void **)&t->d_D32, (void **)&t->d_sc64, (void **)&t->d_sc32, &t->d_tables,
+                      (void **)&t->d_bhpart}) {
         tree_free_block(t, *pp);
         *pp = nullptr;
     }
@@ -914,11 +916,21 @@ static int ensure_expansions(fmm_tree *t, int code, int p, int prec)
     if (e == hipSuccess && t->d_M32)
         e = launch_fill((double *)t->d_M32, (size_t)(nc + 1) * nmp / 2, t->ctx->stream);
     if (e != hipSuccess) FAIL(FMM_EDEVICE, "fill failed: %s", hipGetErrorString(e));
-    // (here, not in the evaluation, which allocates nothing; last, and only
-    // where it fits: without it each group of particles is one wavefront's)
-    if (t->method == FMM_METHOD_BH && !t->d_bhpart && bh_part_doubles(n)) {
-        const size_t bytes = sizeof(double) * bh_part_doubles(n), limit = t->ctx->tree_limit;
-        if (!limit || t->dev_bytes + bytes <= limit) (void)tree_alloc(t, (void **)&t->d_bhpart, bytes);
+    // The sums of groups that several wavefronts share (here, not in the
+    // evaluation, which allocates nothing).  Small ones are the tree's, taken
+    // last and only where they fit beside the buffers of this set-up; larger
+    // ones would outweigh a small tree's buffers, and all trees of the context
+    // share one block.  (Without either each group is one wavefront's.)
+    if (const size_t need = t->method == FMM_METHOD_BH ? bh_part_doubles(n, t->ctx->ncu) : 0) {
+        fmm_ctx *c = t->ctx;
+        const size_t bytes = sizeof(double) * need;
+        if (need <= kBHOwnDoubles && (!c->tree_limit || t->dev_bytes + bytes <= c->tree_limit))
+            (void)tree_alloc(t, (void **)&t->d_bhpart, bytes);
+        if (!t->d_bhpart && !c->bh_part &&
+            hipMallocAsync((void **)&c->bh_part, sizeof(double) * bh_part_max(c->ncu), c->stream) != hipSuccess) {
+            (void)hipGetLastError();
+            c->bh_part = nullptr;
+        }
     }
     t->order = order;
     t->smask = smask;

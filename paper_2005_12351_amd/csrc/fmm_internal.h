@@ -273,6 +273,7 @@ struct fmm_ctx {
     size_t dev_cache_bytes = 0;
     char *arena = nullptr;
     size_t arena_cap = 0;
+    double *bh_part = nullptr;            // Barnes-Hut sums of shared groups, bh_part_max doubles (trees use it in stream order)
     hipEvent_t ev_fork = nullptr;
     std::vector<ProfEntry> prof;
     std::vector<hipEvent_t> ev_pool;
@@ -316,7 +317,7 @@ struct fmm_tree {
     M2LWork m2lwork;
     double *d_cls_geom = nullptr;
     unsigned long long *d_bhcount = nullptr;   // Barnes-Hut interaction counters (2)
-    double *d_bhpart = nullptr;            // sums of wavefronts that share a group (bh_part_doubles; null: none share)
+    double *d_bhpart = nullptr;            // the tree's own sums of shared groups (null: the context's bh_part)
     // per expansion state
     int have_up = 0, order = 0, p = 0, prec = 0, dtab_p = -1;   // order: the lowest source order s
     int smask = 1;                         // source orders present (bit mask)
@@ -409,8 +410,11 @@ hipError_t noalloc_scratch(int device, double **ptr);
 int l2p_harmonic_leaves();              // leaves one L2P wave may take in the harmonic basis
 int l2p_pack_limit(int q, bool cols);   // the same in the full basis at expansion order q, per layout
 bool l2p_columns_pay(int q, int npacks, int ncu);   // L2P layout choice for a launch of npacks waves
-// doubles of the tree's d_bhpart for n particles (0: none used)
-size_t bh_part_doubles(int64_t n);
+// Barnes-Hut sums of shared groups: doubles for n particles (0: no group is
+// shared) and for any number; up to kBHOwnDoubles a tree holds its own
+constexpr size_t kBHOwnDoubles = (size_t)2 << 17;   // 2 MB
+size_t bh_part_doubles(int64_t n, int ncu);
+size_t bh_part_max(int ncu);
 hipError_t launch_bh(fmm_tree *t, int outputs, double *phi, double *field, double *grad, hipStream_t s);
 // P2P over the leaves p2p_order[first .. first + count) (count < 0: to the end)
 hipError_t launch_p2p_part(fmm_tree *t, hipStream_t s, int first, int count);

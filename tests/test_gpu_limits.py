@@ -89,3 +89,86 @@ def test_schedule_given_up_holds_what_the_host_s_does(n, ncrit, theta):
         t.close()
     dev.close()
     host.close()
+
+
+# Barnes-Hut set up at one p and then at a higher one, under a limit that the
+# second reaches without the shared groups' sums: those of the first must not
+# count against it
+def test_barnes_hut_set_up_again_at_a_higher_order(orc):
+    n, ncrit = 2000, 1
+    w = W.small_random(6100, n, 1, "uniform", p=4, theta=0.6, ncrit=ncrit)
+    pos, mom = to_dev(w.pos), to_dev(w.moments)
+
+    def held(p, limit):
+        c = fmm.Context(0)
+        c.set_tree_limit(limit)
+        t = fmm.Tree(c, pos, ncrit, 0.6, fmm.FMM_METHOD_BH)
+        t.upward(1, mom, p, FP64)
+        b = t.info()["bytes"]
+        t.close()
+        c.close()
+        return b
+
+    bare = held(10, held(10, 0) - 1)   # p 10 without the sums
+    assert held(4, 0) < bare           # p 4 has room for them
+    c = fmm.Context(0)
+    c.set_tree_limit(bare)
+    t = fmm.Tree(c, pos, ncrit, 0.6, fmm.FMM_METHOD_BH)
+    out = []
+    for p in (4, 10, 4):
+        t.upward(1, mom, p, FP64)
+        phi, E = t.evaluate()
+        torch.cuda.synchronize()
+        out.append((phi.cpu().numpy(), E.cpu().numpy()))
+    assert np.array_equal(out[0][0], out[2][0]) and np.array_equal(out[0][1], out[2][1])
+    po, Eo = orc.Tree(w.pos, ncrit).bh(1, w.moments, 10, 0.6)[:2]
+    assert within(out[1][0], po, FP64, "phi", floor=PHI_FLOOR) & within(out[1][1], Eo, FP64, "E")
+    t.close()
+    c.close()
+
+
+# larger sums of shared groups belong to the context: they take nothing of a
+# tree's limit or of a request's footprint, and two trees of one context in turn
+# give what each gives alone, also as replayed graphs
+def test_barnes_hut_sums_of_the_context(orc):
+    ctx = fmm.Context(0)
+    trees = []
+    for n, s in ((8192, 1), (20001, 0)):
+        w = W.small_random(6200 + n, n, s, "plummer", p=6, theta=0.6, ncrit=64)
+        own = fmm.Context(0)
+        t = fmm.Tree(own, to_dev(w.pos), 64, 0.6, fmm.FMM_METHOD_BH)
+        t.upward(s, to_dev(w.moments), 6, FP64)
+        phi, E, G = (x.cpu().numpy() for x in t.evaluate_grad())
+        held = t.info()["bytes"]
+        # 8 to 2 wavefronts of 80 bytes a particle would be 5.2 and 3.2 MB more
+        assert held < 8 * n * (3 + 1 + 0.5 + 3 + 4 + 4) + t.info()["ncells"] * (64 + 8 * 52)
+        t.close()
+        own.close()
+        t = fmm.Tree(ctx, to_dev(w.pos), 64, 0.6, fmm.FMM_METHOD_BH)
+        trees.append((t, s, to_dev(w.moments), phi, E, G, [torch.empty_like(torch.from_numpy(x)).cuda() for x in (phi, E, G)]))
+    for _ in range(3):
+        for t, s, mom, phi, E, G, out in trees:
+            t.upward(s, mom, 6, FP64)
+            t.evaluate_grad(fmm.FMM_POT | fmm.FMM_FIELD | fmm.FMM_GRAD, *out)
+        torch.cuda.synchronize()
+        for t, s, mom, phi, E, G, out in trees:
+            for a, b in zip(out, (phi, E, G)):
+                assert np.array_equal(a.cpu().numpy(), b)
+    for x in trees:
+        x[0].close()
+    ctx.close()
+
+
+# a Barnes-Hut request of few cells holds no more than it was admitted with
+@pytest.mark.parametrize("n", [3000, 8192, 32768])
+def test_barnes_hut_request_within_its_footprint(n):
+    w = W.small_random(6300, n, 0, "uniform", p=4, theta=0.5, ncrit=n)
+    ctx = fmm.Context(0, budget_bytes=1 << 30)
+    ctx.serve_start(1)
+    pos, mom = to_dev(w.pos), to_dev(w.moments)
+    phi, E = torch.empty(n, dtype=torch.float64, device="cuda"), torch.empty((n, 3), dtype=torch.float64, device="cuda")
+    k = ctx.submit(n=n, order=0, p=4, theta=0.5, ncrit=n, pos=pos, moments=mom, phi=phi, field=E, method=fmm.FMM_METHOD_BH)
+    ctx.wait(k, 60.0)
+    t = ctx.request_times(k)
+    assert 0 < t["bytes_used"] <= t["footprint"]
+    ctx.close()
