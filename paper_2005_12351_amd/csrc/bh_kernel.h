@@ -71,14 +71,14 @@ __device__ __forceinline__ void wave_sync_bh()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// row places of a wave, and the lanes below which a round waits for more marks
 // lowest p from which cells wait in LDS (harmonic basis).  us with / without
 // places, theta 0.6, Plummer: MIXED p 6, 10^6 dipoles 3550 / 3750, p 4, 100k
 // quadrupoles 790 / 760; MIXED gradient p 8, 100k charges 2489 / 3278, but p 6,
 // 10^6 10588 / 7844; FP64 p 8 1752 / 2488, p 10, 300k dipoles 6701 / 22438, but p
-// 6, 10^6 7911 / 5876; FP64 gradient p 10, 30 011 charges 12002 / 13517, but p 8,
-// 100k 6003 / 5555.
-constexpr int bh_places_from(bool f32, bool grad) { return f32 ? (grad ? 8 : 6) : (grad ? 10 : 8); }
+// 6, 10^6 7911 / 5876; FP64 gradient p 9, 70k charges 11400 / 13900, but p 8,
+// 100k 6003 / 5050.
+constexpr int bh_places_from(bool f32, bool grad) { return f32 ? (grad ? 8 : 6) : (grad ? 9 : 8); }
+// row places of a wave, and the lanes below which a round waits for more marks
 constexpr int kSlots = 32;
 constexpr int kRoundLanes = 36;
 constexpr int kOwnLevel = 3;
@@ -98,8 +98,18 @@ __global__ __launch_bounds__(64) void bh_kernel(BHArgs a)
 {
     constexpr bool F32 = sizeof(T) == 4;
     constexpr bool PLACES = H && P >= bh_places_from(sizeof(T) == 4, GRAD);
+    // FP64 with the gradient: more terms than registers from p 5 or so on
+    // (86 spilled at p 8, 1800 at p 10 in the full basis), and what else lives
+    // through the M2P costs.  These kernels keep the share's numbers in LDS, and
+    // have the M2P written out where the cell is accepted: called, its terms are
+    // ordered before they meet this kernel's registers.  us, 70k Plummer
+    // charges, theta 0.6: p 8 5380 -> 4850, full basis p 8 22 480 -> 20 000, p 10
+    // 104 000 -> 88 600; dipoles p 8 5690 -> 5250, full basis p 10 107 100 -> 89 700
+    // (octupoles of the harmonic basis are better called: p 8 4870 and 4280).
+    constexpr bool FULL = !F32 && GRAD && !PLACES;
+    constexpr bool CALLED = !FULL || (H && S == 3);
     constexpr int W = (S + 1) * (S + 2) / 2;
-    __shared__ int stk_c[kStack];
+    __shared__ int stk_c[kStack], own_[2];
     __shared__ unsigned long long stk_m[kStack];
     const int lane = threadIdx.x;
     const int share = blockIdx.x & (a.split - 1), group = blockIdx.x / a.split;
@@ -115,6 +125,10 @@ __global__ __launch_bounds__(64) void bh_kernel(BHArgs a)
     if (lane == 0) {
         stk_c[0] = 0;
         stk_m[0] = live;
+        if constexpr (FULL) {
+            own_[0] = a.split - 1;
+            own_[1] = share;
+        }
     }
     sp = 1;
     wave_sync_bh();
@@ -195,7 +209,7 @@ __global__ __launch_bounds__(64) void bh_kernel(BHArgs a)
         const bool accept = mine && !inside && (__dmul_rn(r, r) < __dmul_rn(a.theta2, d2));
         const unsigned long long acc_m = __ballot(accept);
         const unsigned long long rest = mask & ~acc_m;
-        const bool own = cell.level >= kOwnLevel || (c & (a.split - 1)) == share;
+        const bool own = cell.level >= kOwnLevel || (c & (FULL ? own_[0] : a.split - 1)) == (FULL ? own_[1] : share);
         if constexpr (PLACES) {
             if (acc_m && own) {
                 if (used == 0xffffffffu) rounds(false);
@@ -215,7 +229,24 @@ __global__ __launch_bounds__(64) void bh_kernel(BHArgs a)
             }
         } else if (accept && own) {
             ++n_m2p;
-            m2p(Mb + (size_t)c * a.nmp, dx, dy, dz, r);
+            if constexpr (CALLED) {
+                m2p(Mb + (size_t)c * a.nmp, dx, dy, dz, r);
+            } else {
+                const double ir = 1.0 / r;
+                T p_, x_, y_, z_, gg[6];
+                const T *Mc = Mb + (size_t)c * a.nmp;
+                const T ux = (T)(dx * ir), uy = (T)(dy * ir), uz = (T)(dz * ir);
+                if constexpr (H) M2PEvalGH<P, S, T>::eval(Mc, ux, uy, uz, p_, x_, y_, z_, gg);
+                else M2PEvalG<P, S, T>::eval(Mc, ux, uy, uz, p_, x_, y_, z_, gg);
+                const double ir3 = ir * ir * ir;
+#pragma unroll
+                for (int q = 0; q < 6; ++q) g[q] -= (double)gg[q] * ir3;
+                ph += (double)p_ * ir;
+                const double ir2 = ir * ir;
+                ex -= (double)x_ * ir2;
+                ey -= (double)y_ * ir2;
+                ez -= (double)z_ * ir2;
+            }
         }
         if (rest) {
             if (cell.nchild == 0) {
@@ -300,7 +331,8 @@ __global__ __launch_bounds__(64) void bh_kernel(BHArgs a)
                 // children in reverse, so that they are visited in octant
                 // order, a lane each; of those at kOwnLevel this wavefront's
                 const bool keep = lane < cell.nchild && (cell.level != kOwnLevel - 1 ||
-                                                         ((cell.child0 + lane) & (a.split - 1)) == share);
+                                                         ((cell.child0 + lane) & (FULL ? own_[0] : a.split - 1)) ==
+                                                             (FULL ? own_[1] : share));
                 const unsigned long long km = __ballot(keep);
                 if (keep) {
                     const int at = sp + __popcll(km >> lane) - 1;   // those after it lie below

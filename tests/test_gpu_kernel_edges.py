@@ -160,7 +160,8 @@ def test_schedule_class_paths(kind, n, ncrit, theta, many):
 
 
 # Barnes-Hut: one wavefront a group, two and eight; rows through places in LDS
-# (p >= 6) and not; a root that is a leaf, a tree that ends above and below the
+# (the MIXED field from p 6 on) and not (the others, from p 8 or 9 on in
+# test_gpu_bh_orders); a root that is a leaf, a tree that ends above and below the
 # level whose cells are shared out, a last group of one particle
 @pytest.mark.parametrize("n,ncrit,p,s,kind", [(1, 8, 6, 0, "uniform"), (40, 64, 6, 1, "uniform"), (65, 8, 6, 1, "uniform"),
                                               (129, 4, 5, 2, "plummer"), (2000, 64, 7, 1, "uniform"),
