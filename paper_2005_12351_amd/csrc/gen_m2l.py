@@ -502,7 +502,8 @@ def gen_kernel_mfma(p, s, opt=None):
     L.append(f"    __shared__ unsigned ixs[{len(words) * 64}];")
     # per wave one or two chunks of the 64 source rows, and the sums of an
     # item's waves when its entries are done
-    L.append(f"    __shared__ float4 area[{max(nbuf * wgw * TILE * NQ, nlp * TILE // 4)}];")
+    # (on a line boundary: the swizzled reads flip address bits 4 to 6)
+    L.append(f"    __shared__ alignas({4 * ROW_LINE}) float4 area[{max(nbuf * wgw * TILE * NQ, nlp * TILE // 4)}];")
     L.append("    float *const red = (float *)area;")
     L.append(f"    for (int k = threadIdx.x; k < {len(words) * 64}; k += {NT}) ixs[k] = kIdx_{name}[k];")
     L.append("    __syncthreads();")
