@@ -23,8 +23,8 @@ __host__ __device__ constexpr int mindex(int nx, int ny, int nz)
 
 constexpr int kMaxLevel = 21;        // 21 bits per axis, 63-bit keys
 constexpr int kTileW = 64;           // targets per M2L tile = wavefront width
-constexpr int kPTable = 12;
-constexpr int kGraphKey = 10;        // arguments a captured launch sequence is keyed by          // multi-index tables cover orders <= 12
+constexpr int kPTable = 12;          // multi-index tables cover orders <= 12
+constexpr int kGraphKey = 10;        // arguments a captured launch sequence is keyed by
 
 struct MultiIndex { int8_t x, y, z, k; };
 
@@ -257,7 +257,6 @@ struct fmm_ctx {
     double *noalloc_scratch = nullptr;    // device address of the static gradient scratch on `device`
     void *pinned = nullptr;               // pinned host staging of tree construction's copies
     size_t pinned_bytes = 0;
-    int64_t *pin_small = nullptr;         // pinned words for the totals a tree build reads back
     // coherent host words a tree build's read-backs arrive in: a one-thread
     // kernel writes the words, then the sequence number sig_seq, which the
     // host polls (tree_gpu.hip, read_words)

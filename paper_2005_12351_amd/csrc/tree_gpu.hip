@@ -957,15 +957,14 @@ __global__ void zero_i32_kernel(int32_t *p, int64_t n)
 }
 
 // ---------------------------------------------------------------- host side
-// Scratch memory of one build.  With a context, blocks come first from its
+// Scratch memory of one build.  Blocks come first from the context's
 // arena by bumping a pointer (a released arena block is reused only by the
 // next build on the same stream, after this one's work); what does not fit
 // comes from the stream-ordered allocator, and the arena grows to this
 // build's total (up to the context's cache limit) for the next build.
 struct Dev {
     hipStream_t s;
-    int64_t *pin = nullptr;   // 8 pinned words for read-backs (or none)
-    fmm_ctx *ctx = nullptr;
+    fmm_ctx *ctx;
     size_t used = 0, need = 0;
     std::vector<void *> blocks;
     hipError_t err = hipSuccess;
@@ -976,7 +975,7 @@ struct Dev {
         if (err != hipSuccess) return nullptr;
         const size_t b = (std::max<size_t>(count, 1) * sizeof(T) + 255) / 256 * 256;
         need += b;
-        if (ctx && ctx->arena && used + b <= ctx->arena_cap) {
+        if (ctx->arena && used + b <= ctx->arena_cap) {
             p = ctx->arena + used;
             used += b;
             return (T *)p;
@@ -997,7 +996,7 @@ struct Dev {
     ~Dev()
     {
         for (void *p : blocks) hipFreeAsync(p, s);
-        if (ctx && need > ctx->arena_cap && err == hipSuccess) {
+        if (need > ctx->arena_cap && err == hipSuccess) {
             // twice this build's need (at least 32 MB), so that builds up to
             // twice as large grow it no further
             const size_t want = std::min(std::max(2 * need, (size_t)32 << 20), ctx_cache_limit(ctx));
@@ -1060,30 +1059,23 @@ __global__ void publish_kernel(const int64_t *__restrict__ src, int n, int64_t *
     __hip_atomic_store(&host[kSigWords], seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// the first k device words (8-byte aligned), read on the host; this waits
-// for the stream's work up to them
+// the first k <= kSigWords device words (8-byte aligned), read on the host;
+// this waits for the stream's work up to them
 hipError_t read_words(Dev &dv, const void *dev, int k, void *host)
 {
-    if (dv.ctx && dv.ctx->sig && k <= kSigWords) {
-        fmm_ctx *c = dv.ctx;
-        const int64_t seq = ++c->sig_seq;
-        hipLaunchKernelGGL(publish_kernel, dim3(1), dim3(64), 0, dv.s, (const int64_t *)dev, k, c->sig_dev, seq);
-        GCHK(hipGetLastError());
-        const auto t0 = std::chrono::steady_clock::now();
-        while (__atomic_load_n(&c->sig[kSigWords], __ATOMIC_ACQUIRE) != seq) {
-            if (std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count() > kSigSpinUs) {
-                GCHK(hipStreamSynchronize(dv.s));
-                if (__atomic_load_n(&c->sig[kSigWords], __ATOMIC_ACQUIRE) != seq) return hipErrorUnknown;
-                break;
-            }
+    fmm_ctx *c = dv.ctx;
+    const int64_t seq = ++c->sig_seq;
+    hipLaunchKernelGGL(publish_kernel, dim3(1), dim3(64), 0, dv.s, (const int64_t *)dev, k, c->sig_dev, seq);
+    GCHK(hipGetLastError());
+    const auto t0 = std::chrono::steady_clock::now();
+    while (__atomic_load_n(&c->sig[kSigWords], __ATOMIC_ACQUIRE) != seq) {
+        if (std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count() > kSigSpinUs) {
+            GCHK(hipStreamSynchronize(dv.s));
+            if (__atomic_load_n(&c->sig[kSigWords], __ATOMIC_ACQUIRE) != seq) return hipErrorUnknown;
+            break;
         }
-        memcpy(host, c->sig, sizeof(int64_t) * k);
-        return hipSuccess;
     }
-    void *dst = dv.pin ? (void *)dv.pin : host;
-    GCHK(hipMemcpyAsync(dst, dev, sizeof(int64_t) * k, hipMemcpyDeviceToHost, dv.s));
-    GCHK(hipStreamSynchronize(dv.s));
-    if (dst != host) memcpy(host, dst, sizeof(int64_t) * k);
+    memcpy(host, c->sig, sizeof(int64_t) * k);
     return hipSuccess;
 }
 
@@ -1166,21 +1158,11 @@ hipError_t sort_long_lists(Dev &dv, const LongList *longs, int64_t nlong, int64_
 }
 
 // host staging of the device-to-host copies: the context's pinned buffer
-// (fast, asynchronous copies), grown on demand, or plain host memory
+// (fast, asynchronous copies), grown on demand
 struct Staging {
     fmm_ctx *ctx;
-    std::vector<char> plain;
     char *base = nullptr;
-    hipError_t reserve(size_t bytes)
-    {
-        if (ctx) {
-            GCHK(ctx_pinned(ctx, bytes, &base));
-        } else {
-            plain.resize(bytes);
-            base = plain.data();
-        }
-        return hipSuccess;
-    }
+    hipError_t reserve(size_t bytes) { return ctx_pinned(ctx, bytes, &base); }
 };
 
 // ------------------------------------------------------------------ M2L scheduling
@@ -1608,36 +1590,30 @@ hipError_t ctx_arena_reserve(fmm_ctx *ctx, size_t bytes)
 }
 
 // Builds the canonical tree (and, when theta > 0, the interaction lists) of
-// the n device positions on stream s, and returns it in host form.  ctx (may
-// be null): its pinned staging buffer and, while profiling, the wall-clock
-// phases.
+// the n device positions on the context's stream s, and returns it in host
+// form.
 hipError_t gpu_build_tree(const double *pos, int64_t n, int ncrit, double theta, bool lists, hipStream_t s,
                           HostTree &t, fmm_ctx *ctx, DevKeep &dt)
 {
     t = HostTree();
     t.n = n;
-    Dev dv{s};
-    if (ctx) {
-        if (!ctx->pin_small) GCHK(hipHostMalloc((void **)&ctx->pin_small, 4096, hipHostMallocDefault));
-        if (!ctx->sig) {
-            GCHK(hipHostMalloc((void **)&ctx->sig, sizeof(int64_t) * (kSigWords + 1),
-                               hipHostMallocCoherent | hipHostMallocMapped));
-            ctx->sig[kSigWords] = ctx->sig_seq;
-            const hipError_t e = hipHostGetDevicePointer((void **)&ctx->sig_dev, ctx->sig, 0);
-            if (e != hipSuccess) {
-                (void)hipHostFree(ctx->sig);
-                ctx->sig = nullptr;
-                return e;
-            }
+    Dev dv{s, ctx};
+    if (!ctx->sig) {
+        GCHK(hipHostMalloc((void **)&ctx->sig, sizeof(int64_t) * (kSigWords + 1),
+                           hipHostMallocCoherent | hipHostMallocMapped));
+        ctx->sig[kSigWords] = ctx->sig_seq;
+        const hipError_t e = hipHostGetDevicePointer((void **)&ctx->sig_dev, ctx->sig, 0);
+        if (e != hipSuccess) {
+            (void)hipHostFree(ctx->sig);
+            ctx->sig = nullptr;
+            return e;
         }
-        dv.pin = ctx->pin_small;
-        dv.ctx = ctx;
     }
     // wall-clock phases for the context's profile (the device work of a
     // phase is counted where the host next waits for it)
     auto t_last = std::chrono::steady_clock::now();
     auto mark = [&](const char *nm) {
-        if (!ctx || !ctx->profile) return;
+        if (!ctx->profile) return;
         const auto now = std::chrono::steady_clock::now();
         ctx->prof.push_back(ProfEntry{nm, nullptr, nullptr, std::chrono::duration<double, std::milli>(now - t_last).count()});
         t_last = now;
