@@ -281,12 +281,23 @@ __global__ __launch_bounds__(kPT, 5) void p2p_f32_kernel(P2PArgs a)
                     auto pairs = [&](auto check) {
                     for (int jj = 0; jj < per; ++jj) {
                         const int j = ja + jj;
-                        const float rx = (float)(tx - sst[j].x), ry = (float)(ty - sst[j].y), rz = (float)(tz - sst[j].z);
-                        const float r2 = __builtin_fmaf(rx, rx, __builtin_fmaf(ry, ry, rz * rz));
-                        const float inv = (decltype(check)::value && j == jself) ? 0.f : __builtin_amdgcn_rsqf(r2);
+                        const P2PStaged<NV> &src = sst[j];
+                        const double sx = src.x, sy = src.y, sz = src.z;
                         float4 mv[NV];
 #pragma unroll
-                        for (int v = 0; v < NV; ++v) mv[v] = sst[j].m[v];
+                        for (int v = 0; v < NV; ++v) mv[v] = src.m[v];
+                        // With octupoles the scheduler would hold back half of
+                        // these reads until the first are used, to keep four
+                        // waves a SIMD, and each pair then waits for LDS twice;
+                        // only arithmetic may pass this point, at the same
+                        // registers.  us held back / at once, dipoles (charges),
+                        // quadrupoles and octupoles: 26 495 Plummer 1501 / 1445
+                        // (1388 / 1276), 40 009 uniform 127 / 122 (115 / 108); all
+                        // four orders, gradient, 40 009 uniform 220 / 216.
+                        if constexpr (NV > 3) __builtin_amdgcn_sched_barrier(1);
+                        const float rx = (float)(tx - sx), ry = (float)(ty - sy), rz = (float)(tz - sz);
+                        const float r2 = __builtin_fmaf(rx, rx, __builtin_fmaf(ry, ry, rz * rz));
+                        const float inv = (decltype(check)::value && j == jself) ? 0.f : __builtin_amdgcn_rsqf(r2);
                         if constexpr (GRAD) {
                             if constexpr (ONE) {
                                 float t6[6];
