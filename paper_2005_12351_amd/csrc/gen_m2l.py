@@ -484,6 +484,17 @@ def gen_kernel_mfma(p, s, opt=None):
     # two chunks in LDS where two workgroups share a CU's 160 KB
     nbuf = 2 if mfma_waves(p, s) == 2 else 1
     assert nbuf == 1 or nchunk >= 3
+    # Kernels whose registers the launch bound just allows: the addresses of the
+    # permutations and LDS reads are made where they are used (the compiler keeps
+    # one a copy and one a quad through the loop otherwise), the class numbers come
+    # through the scalar unit, and with three or four waves a SIMD the scales when
+    # their entry begins.  Spilled registers cost more than their moves: a reload
+    # waits for every copy under way.  us with 28 to 188 bytes spilled / now, theta
+    # 0.3, 100k: quadrupoles p 9 307 / 231, octupoles p 8 166 / 141, p 10 319 / 270,
+    # charges p 10 376 / 364, dipoles p 8 204 / 197.  The kernels with registers to
+    # spare lose 2 to 3 % by it (dipoles p 10 342 / 350).
+    tight = nbuf == 1 or nl > 100
+    late_scales = nbuf == 1
     L = []
     # operand byte offsets, two 16-bit values per word: group 2k in the low half
     words = []
@@ -505,6 +516,11 @@ def gen_kernel_mfma(p, s, opt=None):
     # (on a line boundary: the swizzled reads flip address bits 4 to 6)
     L.append(f"    __shared__ alignas({4 * ROW_LINE}) float4 area[{max(nbuf * wgw * TILE * NQ, nlp * TILE // 4)}];")
     L.append("    float *const red = (float *)area;")
+    if tight:
+        L.append("    const int __attribute__((address_space(4))) *const ucls = "
+                 "(const int __attribute__((address_space(4))) *)a.ucls;")
+    else:
+        L.append("    const int32_t *__restrict__ ucls = a.ucls;")
     L.append(f"    for (int k = threadIdx.x; k < {len(words) * 64}; k += {NT}) ixs[k] = kIdx_{name}[k];")
     L.append("    __syncthreads();")
     L.append("    const float *__restrict__ Mb = (const float *)a.M;")
@@ -537,6 +553,12 @@ def gen_kernel_mfma(p, s, opt=None):
 
     def chunk_copies(src, ci, buf):
         # row 8k + sr is the source of lane 8k + sr
+        if tight:
+            out = ["{", "    int at = 4 * sr;", '    asm volatile("" : "+v"(at));']
+            out += [f"    const int src{k} = __builtin_amdgcn_ds_bpermute(at + {4 * (TILE // NQ) * k}, {src});" for k in range(NQ)]
+            out += [f"    copy_to_lds(Mq + (size_t)src{k} * {nmp} + {ROW_LINE * ci}, stage + {buf} + {TILE * k});"
+                    for k in range(NQ)]
+            return out + ["}"]
         return [f"copy_to_lds(Mq + (size_t)__builtin_amdgcn_ds_bpermute(4 * sr + {4 * (TILE // NQ) * k}, {src}) * {nmp} + "
                 f"{ROW_LINE * ci}, stage + {buf} + {TILE * k});" for k in range(NQ)]
 
@@ -581,13 +603,14 @@ def gen_kernel_mfma(p, s, opt=None):
         return f"({CH4} - flip)" if flips and k else "flip" if flips else str(CH4 * k)
 
     # the first entry's sources, operands, scales and first chunks
-    emit(["int src = 0;"] + [f"float w{gstart[0] + k};" for k in range(ng0)] + [f"float s{o};" for o in ords], 4)
+    emit(["int src = 0;"] + [f"float w{gstart[0] + k};" for k in range(ng0)] +
+         ([] if late_scales else [f"float s{o};" for o in ords]), 4)
     if flips:
         emit(["int flip = 0;"], 4)
     emit(["if (ub < ue) {"], 4)
-    emit([f"src = a.usrc[(size_t)ub * {TILE} + lane];", "const int cls = a.ucls[ub];",
-         f"const char *__restrict__ Dr = Db + (size_t)cls * {nd * 4};"] + operands(0, "Dr", "") + scales("", "cls") +
-         [SB], 8)
+    emit([f"src = a.usrc[(size_t)ub * {TILE} + lane];", "const int cls = ucls[ub];",
+         f"const char *__restrict__ Dr = Db + (size_t)cls * {nd * 4};"] + operands(0, "Dr", "") +
+         ([] if late_scales else scales("", "cls")) + [SB], 8)
     for ci in range(nbuf):
         emit(chunk_copies("src", ci, buf(ci)), 8)
     emit(["}"], 4)
@@ -602,9 +625,11 @@ def gen_kernel_mfma(p, s, opt=None):
               "}"], 8)
     emit(["// the entry loaded ahead (this one again at the end of the range)",
           "const int un = u + 1 < ue ? u + 1 : u;",
-          "const int cls = a.ucls[u], clsn = a.ucls[un];",
+          "const int cls = ucls[u], clsn = ucls[un];",
           f"const char *__restrict__ Dr = Db + (size_t)cls * {nd * 4};",
           f"const char *__restrict__ Drn = Db + (size_t)clsn * {nd * 4};"], 8)
+    if late_scales:
+        emit(scales("const float ", "cls"), 8)
     # where the operands are loaded: with registers to spare all but the first
     # chunk's one phase after their registers fall free, the next entry's in
     # the second phase (the later ones are too short to cover the loads);
@@ -620,21 +645,25 @@ def gen_kernel_mfma(p, s, opt=None):
         quads = sorted(set(j // 4 for j in chunks[ci]))
         emit([SB, f"wait_copies<{NQ * (nbuf - 1)}>();", SB] + [f"f32x4 v{q};" for q in quads], 8)
         outs = ", ".join(f'"=&v"(v{q})' for q in quads)
-        ins = ", ".join(f'"v"((srd + 16 * {buf(ci)}) ^ {16 * (q - NQ * ci)}u)' for q in quads)
+        ins = ", ".join(f'"v"(({"rd" if tight else "srd"} + 16 * {buf(ci)}) ^ {16 * (q - NQ * ci)}u)' for q in quads)
         code = "".join(f"ds_read_b128 %{k}, %{k + len(quads)}\\n" for k in range(len(quads))) + "s_waitcnt lgkmcnt(0)"
-        emit([f'asm volatile("{code}" : {outs} : {ins} : "memory");', SB], 8)
+        read = [f'asm volatile("{code}" : {outs} : {ins} : "memory");']
+        if tight:
+            read = ["{", "    unsigned rd = srd;", '    asm volatile("" : "+v"(rd));', "    " + read[0], "}"]
+        emit(read + [SB], 8)
         if ci == 0:
             emit([f"const int srcn = a.usrc[(size_t)un * {TILE} + lane];"], 8)
         for cj in range(1, nchunk):
             if ci == (min(cj - 1, 1) if early else cj - 1):
                 emit(operands(cj, "Dr", "const float "), 8)
         if ci == ahead:
-            emit(operands(0, "Drn", "const float ", "n") + scales("const float ", "clsn", "n"), 8)
+            emit(operands(0, "Drn", "const float ", "n") +
+                 ([] if late_scales else scales("const float ", "clsn", "n")), 8)
         cn, an = (ci + nbuf) % nchunk, (ci + nbuf) // nchunk
         emit([SB] + chunk_copies("srcn" if an else "src", cn, buf(cn, an)), 8)
         emit(mfmas(ci), 8)
     emit(["src = srcn;"] + [f"w{gstart[0] + k} = w{gstart[0] + k}n;" for k in range(ng0)] +
-         [f"s{o} = s{o}n;" for o in ords], 8)
+         ([] if late_scales else [f"s{o} = s{o}n;" for o in ords]), 8)
     if flips:
         emit([f"flip = {CH4} - flip;"], 8)
     emit(["}"], 4)
