@@ -75,9 +75,13 @@ __device__ __forceinline__ void wave_sync_bh()
 // places, theta 0.6, Plummer: MIXED p 6, 10^6 dipoles 3550 / 3750, p 4, 100k
 // quadrupoles 790 / 760; MIXED gradient p 8, 100k charges 2489 / 3278, but p 6,
 // 10^6 10588 / 7844; FP64 p 8 1752 / 2488, p 10, 300k dipoles 6701 / 22438, but p
-// 6, 10^6 7911 / 5876; FP64 gradient p 9, 70k charges 11400 / 13900, but p 8,
-// 100k 6003 / 5050.
-constexpr int bh_places_from(bool f32, bool grad) { return f32 ? (grad ? 8 : 6) : (grad ? 9 : 8); }
+// 6, 10^6 7911 / 5876; FP64 gradient p 9, 70k charges 10530 / 11310, quadrupoles
+// 9900 / 12370, octupoles 10220 / 10590, but dipoles 11410 / 10340 (their kernel
+// spills a third more with places), and charges p 8, 100k 6003 / 5050.
+constexpr int bh_places_from(bool f32, bool grad, int s)
+{
+    return f32 ? (grad ? 8 : 6) : (grad ? (s == 1 ? 10 : 9) : 8);
+}
 // row places of a wave, and the lanes below which a round waits for more marks
 constexpr int kSlots = 32;
 constexpr int kRoundLanes = 36;
@@ -97,7 +101,7 @@ template <int P, int S, typename T, bool H, bool GRAD>
 __global__ __launch_bounds__(64) void bh_kernel(BHArgs a)
 {
     constexpr bool F32 = sizeof(T) == 4;
-    constexpr bool PLACES = H && P >= bh_places_from(sizeof(T) == 4, GRAD);
+    constexpr bool PLACES = H && P >= bh_places_from(F32, GRAD, S);
     // FP64 with the gradient: more terms than registers from p 5 or so on
     // (86 spilled at p 8, 1800 at p 10 in the full basis), and what else lives
     // through the M2P costs.  These kernels keep the share's numbers in LDS, and

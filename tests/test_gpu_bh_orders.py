@@ -1,5 +1,5 @@
 """Barnes-Hut at the orders from which cells wait in LDS (MIXED field p 6,
-gradient 8; FP64 field 8, gradient 9), with one and two wavefronts a group of
+gradient 8; FP64 field 8, gradient 9, of dipoles 10), with one and two wavefronts a group of
 particles, and the FP64 gradient just below, where the M2P is written out (both
 bases, charges to octupoles), against the oracle."""
 import numpy as np
@@ -57,3 +57,11 @@ def test_fp64_gradient_written_out(orc, order, p, basis, n):
         W.small_random(7100 + order, n, order, "plummer", p=p, theta=0.5, ncrit=8)
     print(f"[bh fp64 gradient] order={order} p={p} basis={basis} n={n}", flush=True)
     _check(orc, w, w.order, n, 8, p, FP64, basis, 300)
+
+
+# dipoles at p 9: the one order and p whose gradient waits with places only from the next p on
+@pytest.mark.parametrize("n,ncrit", [(130, 8), (2000, 8), (20001, 32), (40000, 64)])
+def test_fp64_gradient_dipoles_below_places(orc, n, ncrit):
+    w = W.small_random(7200 + n, n, 1, "plummer", p=9, theta=0.5, ncrit=ncrit)
+    print(f"[bh fp64 gradient] dipoles p=9 n={n}", flush=True)
+    _check(orc, w, 1, n, ncrit, 9, FP64, fmm.FMM_M2L_HARMONIC, 300)
